@@ -31,8 +31,14 @@ void clear_error();
     } while (0)
 
 // ---------------------------------------------------------------- device descriptors
+// Pointer to device memory.  An address that comes out of a descriptor is a
+// generic pointer to the compiler, whose (flat) loads can only be waited for all
+// at once; a load through this type can be in flight behind later ones.
+typedef const __attribute__((address_space(1))) double *gptr;
+__host__ __device__ inline gptr as_global(uint64_t a) { return (gptr)(uintptr_t)a; }
+
 // Where a GEMM operand lives.
-enum : int16_t {
+enum : int32_t {
     OPD_ABS = 0,  // absolute device address (operator blocks, plan-owned copies)
     OPD_IN = 1,   // element offset into the call's input vector (psi, or gbar in the adjoint)
     OPD_TMP = 2   // element offset into the plan's intermediate buffer
@@ -62,9 +68,10 @@ struct Seg {
     int32_t K;
     int32_t K2;   // fused: width of the intermediate
     int32_t ldr;  // fused: row length of the B block
-    int16_t pkind, qkind;
-    int16_t ptrans, qtrans;
-    int16_t fused, pad16;
+    // (32 bits each: a narrower field would be fetched through the vector memory path)
+    int32_t pkind, qkind;
+    int32_t ptrans, qtrans;
+    int32_t fused;
     int32_t coef;  // global coefficient index, -1 = 1.0
     int32_t term;  // global term index (for coefficient gradients), -1 = none
     double w = 1.0;  // constant factor of the contribution
@@ -92,8 +99,10 @@ struct Task {
     int32_t row0, col0;
     int32_t m, n;      // rows / columns of this tile (<= tile size)
     int32_t member;
-    int32_t part0;     // first coefficient-gradient partial slot of this task
+    int32_t part0;     // adjoint output tiles: first partial slot of the tile's diagonal terms
     int32_t rslot;     // output-tile tasks: Rayleigh partial row (member-contiguous)
+    int32_t nitem;     // wide passes: items of the tile's contraction (see Split)
+    int32_t pad;
 };
 
 // ---------------------------------------------------------------- host metadata
@@ -132,10 +141,21 @@ struct Record {
     double w;
 };
 
+// One run of a wide tile's contraction: its segments' items of 16 (a copy
+// segment is one item) in list order, cut into TWA (intermediates) or TWB
+// (outputs) runs whose lengths differ by at most one.
+constexpr int TWA = 4, TWB = 8;
+struct Split {
+    int32_t seg, kb;  // first segment with an item of the run, and that item's index in it
+    int32_t n;        // items of the run
+    int32_t part;     // adjoint output tiles: the run's first coefficient-gradient slot (one per segment it meets)
+};
+
 struct Lists {  // device task lists of one pass
     Task *tasks = nullptr;
     int32_t ntask = 0;
     int32_t ns = 1;  // 16 x 16 sub-tiles per tile side: 1 when every tile fits 16 x 16, else 2
+    Split *splits = nullptr;  // passes of 32-wide tiles: [ntask * TWA] (stage A) or [ntask * TWB]
 };
 
 struct PassSet {  // everything one projection direction needs in one precision
@@ -145,7 +165,7 @@ struct PassSet {  // everything one projection direction needs in one precision
     DiagTerm *diags = nullptr;
     int32_t nseg = 0, ndiag = 0;
     int64_t tmp_elems = 0;  // intermediate buffer length (elements)
-    int32_t npart = 0;      // coefficient-gradient partials (forward only)
+    int32_t wide = 0;       // side of the pass's tiles in tiles.hip, 0: the kernels of project.hip
 };
 
 // One low-precision operator copy made at plan creation.
@@ -197,7 +217,7 @@ struct dmrg_plan {
     std::vector<int32_t> out_member;
     // device pass sets: [prec slot][direction]  slot 0 = F64, slot 1 = plan precision
     dmrg::PassSet fwd[2], adj[2];
-    // coefficient-gradient reduction (forward F64 pass): CSR over global terms
+    // coefficient-gradient reduction (adjoint pass): CSR over global terms
     int32_t *d_term_ptr = nullptr;
     int32_t *d_term_ent = nullptr;
     double *d_partials = nullptr;
@@ -243,8 +263,9 @@ dmrg_status launch_project(dmrg_plan *plan, int slot, const double *coef, const 
 dmrg_status launch_diag_fold(dmrg_plan *plan, int slot, const double *coef, double *out, hipStream_t s);
 dmrg_status launch_adjoint(dmrg_plan *plan, const double *coef, const double *in, double *out,
                            hipStream_t s);
-dmrg_status launch_gcoef(dmrg_plan *plan, const double *psi, const double *gbar, double *gcoef,
-                         hipStream_t s);
+// gcoef, and gpsi unless null, in one adjoint pass (coef may be null without gpsi)
+dmrg_status launch_gcoef(dmrg_plan *plan, const double *coef, const double *psi, const double *gbar, double *gpsi,
+                         double *gcoef, hipStream_t s);
 dmrg_status launch_convert_jobs(const ConvJob *jobs, int njob, int prec, hipStream_t s);
 dmrg_status launch_diagonal(dmrg_plan *plan, const double *coef, double *diag, hipStream_t s);
 // four vectors in one launch where the plan's tiles allow it (else one launch each);
@@ -252,6 +273,11 @@ dmrg_status launch_diagonal(dmrg_plan *plan, const double *coef, double *diag, h
 constexpr int PROJ_NVEC = 4;
 dmrg_status launch_project_multi(dmrg_plan *plan, const double *coef, const double *in, int64_t in_stride,
                                  double *out, int64_t out_stride, const int32_t *vmask, hipStream_t s);
+// tiles.hip: a wide FP64 pass (both stages).  xg, partials: adjoint passes that
+// also form the coefficient-gradient partials <xg, segment product> (out may be null then)
+dmrg_status launch_tiles(const PassSet &ps, const double *coef, const double *in, double *tmp, double *out,
+                         hipStream_t s, const int32_t *mask, const double *dfold, const RayArgs *ray,
+                         const double *xg = nullptr, double *partials = nullptr);
 // davidson.hip
 dmrg_status davidson_free(dmrg_plan *plan);
 // bytes of the Davidson arrays of a subspace of kmax vectors (the pieces

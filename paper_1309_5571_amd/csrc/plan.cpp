@@ -246,6 +246,8 @@ static dmrg_status analyse(const dmrg_problem *p, MemberPairs *mp_out, std::vect
 
 struct HostPass {
     std::vector<Task> A, B;
+    std::vector<Split> splitA, splitB;  // wide passes
+    int wide = 0;                       // see PassSet
     std::vector<Seg> segs;
     std::vector<DiagTerm> diags;
     int64_t tmp = 0;
@@ -256,9 +258,15 @@ static uint64_t U(const void *p) { return (uint64_t)(uintptr_t)p; }
 // Largest intermediate width a fused two-sided segment keeps in LDS (16 rows x 64).
 constexpr int64_t FUSE_MAX_K2 = 64;
 
-static void add_tiles(std::vector<Task> &out, int64_t rows, int64_t cols, int64_t c_off, int64_t x_off, int64_t ld,
-                      int32_t seg_b, int32_t seg_e, int32_t d_b, int32_t d_e, int member) {
-    int ts = tile_for(rows, cols);
+// 64 x 64 tiles from this many of them on.  Members of m = 256 .. 1536: 173 tiles
+// 60 us with 32 x 32 tiles, 84 us with 64 x 64; 320: 90, 91; 472: 123, 106; 627:
+// 151, 120; 1227: 283, 181.  Members of m = 300 .. 512: 288 tiles 43, 41; 576: 75, 55.
+constexpr int64_t WIDE64_MIN = 320;
+
+// Tiles of side ts (0: by the tile table) of one output matrix.
+static void add_tiles(std::vector<Task> &out, int ts, int64_t rows, int64_t cols, int64_t c_off, int64_t x_off,
+                      int64_t ld, int32_t seg_b, int32_t seg_e, int32_t d_b, int32_t d_e, int member) {
+    if (!ts) ts = tile_for(rows, cols);
     for (int64_t r0 = 0; r0 < rows; r0 += ts)
         for (int64_t c0 = 0; c0 < cols; c0 += ts) {
             Task t{};
@@ -300,6 +308,95 @@ static void sort_tasks(std::vector<Task> &v, const std::vector<Seg> &segs) {
     v.swap(o);
 }
 
+// Items of a segment of a wide pass (a copy is one).
+static int seg_items(const Seg &s) { return s.fused == 2 ? 1 : (s.K + 15) / 16; }
+
+// Task order of a wide stage.  Workgroup b runs on XCD b mod 8.  The tiles of
+// an output matrix (they share operator and input rows) stay together on one
+// XCD, in pieces of at most a sixteenth of the work, largest piece first to
+// the least loaded XCD; inside an XCD the largest tiles start first.
+static void order_for_xcds(std::vector<Task> &v) {
+    constexpr int NX = 8;
+    // a tile's time follows its items whatever part of the tile is inside the
+    // matrix; start and end of a tile take about as long as eight of them
+    auto cost = [&](int i) { return v[i].nitem + 8.0; };
+    double total = 0.0;
+    for (size_t i = 0; i < v.size(); ++i) total += cost((int)i);
+    struct Piece {
+        double cost;
+        int b, e;
+    };
+    std::vector<Piece> pieces;
+    for (int i = 0; i < (int)v.size(); ++i) {
+        if (pieces.empty() || v[i].c_off != v[pieces.back().b].c_off || pieces.back().cost + cost(i) > total / (2 * NX))
+            pieces.push_back(Piece{0.0, i, i});
+        pieces.back().cost += cost(i);
+        pieces.back().e = i + 1;
+    }
+    std::stable_sort(pieces.begin(), pieces.end(), [](const Piece &a, const Piece &b) { return a.cost > b.cost; });
+    std::vector<int> group[NX];
+    double load[NX] = {};
+    for (const Piece &p : pieces) {
+        const int x = (int)(std::min_element(load, load + NX) - load);
+        load[x] += p.cost;
+        for (int i = p.b; i < p.e; ++i) group[x].push_back(i);
+    }
+    for (auto &g : group) std::stable_sort(g.begin(), g.end(), [&](int a, int b) { return v[a].nitem > v[b].nitem; });
+    std::vector<Task> o;
+    o.reserve(v.size());
+    size_t at[NX] = {};
+    while (o.size() < v.size()) {
+        int x = (int)(o.size() % NX);
+        if (at[x] == group[x].size())  // this XCD's tiles are placed: take one from where most are left
+            for (int y = 0; y < NX; ++y)
+                if (group[y].size() - at[y] > group[x].size() - at[x]) x = y;
+        o.push_back(v[group[x][at[x]++]]);
+    }
+    v.swap(o);
+}
+
+// The TW runs of every tile of a wide stage, in task order.  With slots, the
+// coefficient-gradient partials are numbered too: one per run and segment,
+// then one per diagonal term of the tile (Task::part0), listed per term.
+static void make_splits(int TW, std::vector<Task> &tasks, const std::vector<Seg> &segs, std::vector<Split> &out,
+                        const std::vector<DiagTerm> *diags, std::vector<std::vector<int32_t>> *per_term,
+                        int32_t *npart) {
+    int32_t part = 0;
+    out.reserve(out.size() + tasks.size() * TW);
+    for (Task &t : tasks) {
+        const int64_t total = t.nitem;
+        int s = t.seg_begin, kb = 0;
+        for (int w = 0; w < TW; ++w) {
+            int64_t n = total * (w + 1) / TW - total * w / TW;
+            Split sp{s, kb, (int32_t)n, part};
+            bool first = true;
+            while (n > 0) {
+                const int left = seg_items(segs[s]) - kb;
+                if (left == 0) {
+                    ++s;
+                    kb = 0;
+                    continue;
+                }
+                if (first) sp.seg = s, sp.kb = kb;
+                first = false;
+                if (per_term) {
+                    if (segs[s].term >= 0) (*per_term)[segs[s].term].push_back(part);
+                    ++part;
+                }
+                const int take = (int)std::min<int64_t>(n, left);
+                kb += take;
+                n -= take;
+            }
+            out.push_back(sp);
+        }
+        t.part0 = part;
+        if (per_term)
+            for (int d = t.diag_begin; d < t.diag_end; ++d, ++part)
+                if ((*diags)[d].term >= 0) (*per_term)[(*diags)[d].term].push_back(part);
+    }
+    if (npart) *npart = part;
+}
+
 // Low-precision copies of operator blocks: (op, blk, variant) -> device address.
 struct LowStore {
     struct Job {
@@ -335,6 +432,19 @@ static void build_pass(const dmrg_plan *plan, bool adjoint, LowStore *low, uint6
     for (int r = 0; r < (int)plan->records.size(); ++r) {
         const Record &rc = plan->records[r];
         by_out[adjoint ? rc.oin : rc.oout].push_back(r);
+    }
+    // FP64 passes with a tile wider than 16, and every adjoint pass, run on the wide
+    // tiles; reduced precisions and all-16 forward passes (whose two-sided records
+    // fuse into one launch) keep the kernels of project.hip.  A tile table of one
+    // class asks for one tile size whatever else is in the plan (a member's result is
+    // then the same bits alone and in a batch): no 64 x 64 tiles there.
+    if (!low) {
+        hp.wide = adjoint ? 32 : 0;
+        for (const Geo &g : plan->out_geo)
+            if (tile_for(g.rows, g.cols) > 16) hp.wide = 32;
+        int64_t n64 = 0;
+        for (const Geo &g : plan->out_geo) n64 += ((g.rows + 63) / 64) * ((g.cols + 63) / 64);
+        if (hp.wide && !adjoint && g_ncls != 1 && n64 >= WIDE64_MIN) hp.wide = 64;
     }
     auto blk_addr = [&](const OpBlock &b, int variant) -> uint64_t {
         if (!low) return U(b.data);
@@ -419,7 +529,7 @@ static void build_pass(const dmrg_plan *plan, bool adjoint, LowStore *low, uint6
                         dt.w = rc.w;
                         hp.diags.push_back(dt);
                     }
-                } else if (tile_for(go.rows, go.cols) == 16 && dk <= FUSE_MAX_K2) {
+                } else if (!hp.wide && tile_for(go.rows, go.cols) == 16 && dk <= FUSE_MAX_K2) {
                     // small intermediate: fused in the output tile (no stage-A task)
                     s.fused = 1;
                     s.p = blk_addr(rc.a, 0);
@@ -555,15 +665,27 @@ static void build_pass(const dmrg_plan *plan, bool adjoint, LowStore *low, uint6
                 }
             }
         }
+        // (an empty contraction adds nothing, and the wide kernels take none)
+        hp.segs.erase(std::remove_if(hp.segs.begin() + seg_b, hp.segs.end(),
+                                     [](const Seg &s) { return s.fused == 0 && s.K == 0; }),
+                      hp.segs.end());
         int seg_e = (int)hp.segs.size();
-        add_tiles(hp.B, go.rows, go.cols, go.off, go.off, go.ld, seg_b, seg_e, d_b, (int)hp.diags.size(), member);
+        add_tiles(hp.B, hp.wide, go.rows, go.cols, go.off, go.off, go.ld, seg_b, seg_e, d_b, (int)hp.diags.size(), member);
     }
     int baseA = (int)hp.segs.size();
     hp.segs.insert(hp.segs.end(), segsA.begin(), segsA.end());
     for (const TMat &tm : tmats)
-        add_tiles(hp.A, tm.rows, tm.cols, tm.off, 0, tm.cols, baseA + tm.seg, baseA + tm.seg + 1, 0, 0, tm.member);
-    sort_tasks(hp.A, hp.segs);
-    sort_tasks(hp.B, hp.segs);
+        add_tiles(hp.A, hp.wide, tm.rows, tm.cols, tm.off, 0, tm.cols, baseA + tm.seg, baseA + tm.seg + 1, 0, 0, tm.member);
+    if (hp.wide) {
+        for (std::vector<Task> *v : {&hp.A, &hp.B})
+            for (Task &t : *v)
+                for (int s = t.seg_begin; s < t.seg_end; ++s) t.nitem += seg_items(hp.segs[s]);
+        order_for_xcds(hp.A);
+        order_for_xcds(hp.B);
+    } else {
+        sort_tasks(hp.A, hp.segs);
+        sort_tasks(hp.B, hp.segs);
+    }
 }
 
 template <class T>
@@ -596,6 +718,9 @@ static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, hipSt
         if (t.m > 16 || t.n > 16) ps.stageA.ns = 2;
     for (const Task &t : hp.B)
         if (t.m > 16 || t.n > 16) ps.stageB.ns = 2;
+    ps.wide = hp.wide;
+    DMRG_TRY(upload(plan, hp.splitA, &ps.stageA.splits, s));
+    DMRG_TRY(upload(plan, hp.splitB, &ps.stageB.splits, s));
     ps.nseg = (int32_t)hp.segs.size();
     ps.ndiag = (int32_t)hp.diags.size();
     ps.tmp_elems = hp.tmp;
@@ -732,15 +857,17 @@ dmrg_status build_plan(dmrg_plan *plan, int32_t nprob, const dmrg_problem *probs
 }
 
 // Scratch of an analysed plan: intermediate-buffer elements (largest over the
-// passes), coefficient-gradient partial slots (one per segment and diagonal
-// term of every forward FP64 stage-B task) and the largest stage-B task count.
+// passes), coefficient-gradient partial slots (adjoint stage B) and the
+// largest stage-B task count.
 static void scratch_sizes(const dmrg_plan *plan, int32_t prec, int64_t *tmp, int32_t *npart, int32_t *tiles) {
     HostPass f64, a64;
     build_pass(plan, false, nullptr, 0, f64);
     build_pass(plan, true, nullptr, 0, a64);
     int64_t t = std::max(f64.tmp, a64.tmp);
     int32_t part = 0;
-    for (const Task &k : f64.B) part += (k.seg_end - k.seg_begin) + (k.diag_end - k.diag_begin);
+    std::vector<std::vector<int32_t>> per_term(plan->nterm_total);
+    std::vector<Split> splits;
+    make_splits(TWB, a64.B, a64.segs, splits, &a64.diags, &per_term, &part);
     int32_t tl = std::max<int32_t>(1, (int32_t)f64.B.size());
     if (prec != DMRG_F64) {
         LowStore ls;
@@ -781,22 +908,16 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
     HostPass f64, a64;
     build_pass(plan, false, nullptr, 0, f64);
     build_pass(plan, true, nullptr, 0, a64);
-    // coefficient-gradient partial slots (forward FP64 stage B)
+    if (f64.wide == 32) {
+        make_splits(TWA, f64.A, f64.segs, f64.splitA, nullptr, nullptr, nullptr);
+        make_splits(TWB, f64.B, f64.segs, f64.splitB, nullptr, nullptr, nullptr);
+    }
+    make_splits(TWA, a64.A, a64.segs, a64.splitA, nullptr, nullptr, nullptr);
+    // coefficient-gradient partial slots (adjoint stage B)
     {
         int32_t part = 0;
         std::vector<std::vector<int32_t>> per_term(plan->nterm_total);
-        for (Task &t : f64.B) {
-            t.part0 = part;
-            for (int s = t.seg_begin; s < t.seg_end; ++s) {
-                if (f64.segs[s].term >= 0) per_term[f64.segs[s].term].push_back(part);
-                ++part;
-            }
-            for (int d = t.diag_begin; d < t.diag_end; ++d) {
-                if (f64.diags[d].term >= 0) per_term[f64.diags[d].term].push_back(part);
-                ++part;
-            }
-        }
-        plan->fwd[0].npart = part;
+        make_splits(TWB, a64.B, a64.segs, a64.splitB, &a64.diags, &per_term, &part);
         std::vector<int32_t> ptr(1, 0), ent;
         for (auto &v : per_term) {
             ent.insert(ent.end(), v.begin(), v.end());

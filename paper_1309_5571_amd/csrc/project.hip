@@ -26,6 +26,7 @@
 
 #include "internal.h"
 #include "lanes.h"
+#include "terms.h"
 
 namespace dmrg {
 
@@ -521,20 +522,6 @@ __device__ __forceinline__ void zero_acc(typename Tr<PREC>::acc_t (&acc)[2][2]) 
         for (int b = 0; b < 2; ++b) acc[a][b] = typename Tr<PREC>::acc_t{0, 0, 0, 0};
 }
 
-// diagonal-term contribution at output element (rr, cc) of a task's pair
-__device__ __forceinline__ double diag_sum(const DiagTerm *__restrict__ diags, int d0, int d1,
-                                           const double *__restrict__ coef, double x, int64_t rr, int64_t cc) {
-    double val = 0.0;
-    for (int d = d0; d < d1; ++d) {
-        const DiagTerm dt = diags[d];
-        double w = (coef ? coef[dt.coef] : 1.0) * dt.w * x;
-        if (dt.vl) w *= ((const double *)(uintptr_t)dt.vl)[rr * dt.sl];
-        if (dt.vr) w *= ((const double *)(uintptr_t)dt.vr)[cc * dt.sr];
-        val += w;
-    }
-    return val;
-}
-
 // Copy segment (fused = 2) on a tile: v = pscale[r] qscale[c] X(r, c) for the
 // tile's elements in the accumulator layout (zero outside the tile), X the
 // input sub-matrix at s.q with rows s.ldq apart.  FP64 in every precision.
@@ -565,10 +552,8 @@ __device__ __forceinline__ void copy_item(double (&v)[NS][NS][4], const Seg &s, 
 
 // MODE 0: write the intermediate (store_t) of stage A.
 // MODE 1: write FP64 output tiles with the diagonal epilogue (stage B).
-// MODE 2: coefficient-gradient partials <gbar, segment product> per segment
-//         and per diagonal term (stage B task list of the FP64 pass).
 // A workgroup of PW wavefronts owns one output tile at a time (a persistent
-// grid walks the cost-sorted task list).  In modes 0/1 the work items of a
+// grid walks the cost-sorted task list).  The work items of a
 // tile -- (segment, kc_of<PREC>()-long slice of its contraction) in list order -- are
 // dealt round-robin to the wavefronts; the PW partial tiles are summed in a
 // fixed order through LDS, so results do not depend on scheduling.
@@ -576,8 +561,7 @@ template <int PREC, int MODE, int NS>
 __device__ __forceinline__ void tasks_run(const Task *__restrict__ tasks, int ntask, const Seg *__restrict__ segs,
                                           const DiagTerm *__restrict__ diags, const double *__restrict__ in,
                                           const void *__restrict__ tmp, void *__restrict__ out,
-                                          const double *__restrict__ coef, const double *__restrict__ gbar,
-                                          double *__restrict__ partials, const int32_t *__restrict__ mask,
+                                          const double *__restrict__ coef, const int32_t *__restrict__ mask,
                                           const double *__restrict__ dfold, RayArgs ray, double *smem_tasks) {
     typedef Tr<PREC> T;
     double(*red)[32][33] = reinterpret_cast<double(*)[32][33]>(smem_tasks);
@@ -589,50 +573,6 @@ __device__ __forceinline__ void tasks_run(const Task *__restrict__ tasks, int nt
         const Task tk = tasks[t];
         if (mask && !mask[tk.member]) continue;
         const int nsr = (tk.m + 15) >> 4, nsc = (tk.n + 15) >> 4;
-        if (MODE == 2) {
-            // one wavefront per segment: each partial slot has exactly one writer
-            for (int si = tk.seg_begin + wave; si < tk.seg_end; si += PW) {
-                const Seg s = segs[si];
-                typename T::acc_t acc[2][2];
-                double cv[NS][NS][4];
-                zero_acc<PREC>(acc);
-                if (s.fused == 2) {
-                    copy_item<PREC, NS>(cv, s, tk, in);
-                } else if (s.fused) {
-                    fused_item<PREC, NS>(acc, s, tk, in, &red[wave][0][0], nsc);
-                } else {
-                    // one wavefront runs every work item of the segment (PW-strided item loop, 4 passes)
-                    for (int f = 0; f < PW; ++f)
-                        seg_dispatch<PREC, NS>(acc, s, tk, in, tmp, nsr, nsc, f, (s.K + kc_of<PREC>() - 1) / kc_of<PREC>());
-                }
-                double part = 0.0;
-#pragma unroll
-                for (int a = 0; a < NS; ++a)
-#pragma unroll
-                    for (int b = 0; b < NS; ++b)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int r = a * 16 + T::row(g, v), c = b * 16 + r16;
-                            if (a < nsr && b < nsc && r < tk.m && c < tk.n)
-                                part += (s.fused == 2 ? cv[a][b][v] : (double)acc[a][b][v]) *
-                                        gbar[tk.c_off + (int64_t)(tk.row0 + r) * tk.ldc + tk.col0 + c];
-                        }
-                part = wave_sum(part) * s.w;
-                if (lane == 0) partials[tk.part0 + (si - tk.seg_begin)] = part;
-            }
-            const int nseg = tk.seg_end - tk.seg_begin;
-            for (int d = tk.diag_begin + wave; d < tk.diag_end; d += PW) {
-                double part = 0.0;
-                for (int e = lane; e < tk.m * tk.n; e += 64) {
-                    const int64_t rr = tk.row0 + e / tk.n, cc = tk.col0 + e % tk.n;
-                    const int64_t o = tk.c_off + rr * tk.ldc + cc;
-                    part += diag_sum(diags, d, d + 1, nullptr, in[tk.x_off + rr * tk.ldc + cc], rr, cc) * gbar[o];
-                }
-                part = wave_sum(part);
-                if (lane == 0) partials[tk.part0 + nseg + (d - tk.diag_begin)] = part;
-            }
-            continue;
-        }
         // epilogue inputs (folded diagonal and the matching input entries) are
         // fetched before the GEMM work so their latency overlaps it
         constexpr int NQ = NS * NS;  // tile elements per thread: (16 NS)^2 / (64 PW)
@@ -1012,17 +952,17 @@ __global__ __launch_bounds__(64 * PW) __attribute__((amdgpu_waves_per_eu(2))) vo
 #define DMRG_TASK_ARGS                                                                                          \
     const Task *__restrict__ tasks, int ntask, const Seg *__restrict__ segs, const DiagTerm *__restrict__ diags, \
         const double *__restrict__ in, const void *__restrict__ tmp, void *__restrict__ out,                     \
-        const double *__restrict__ coef, const double *__restrict__ gbar, double *__restrict__ partials,          \
-        const int32_t *__restrict__ mask, const double *__restrict__ dfold, RayArgs ray
-#define DMRG_TASK_PASS tasks, ntask, segs, diags, in, tmp, out, coef, gbar, partials, mask, dfold, ray, smem_tasks
+        const double *__restrict__ coef, const int32_t *__restrict__ mask, const double *__restrict__ dfold,     \
+        RayArgs ray
+#define DMRG_TASK_PASS tasks, ntask, segs, diags, in, tmp, out, coef, mask, dfold, ray, smem_tasks
 
 // The task kernel.  The 16x16-tile forward variants are held to two
 // workgroups per CU (at most 256 registers per lane): a pass has a few hundred
 // tiles, and with one workgroup per CU the second half would wait a round.
-template <int PREC, int MODE, int NS>
+template <int PREC, int MODE>
 __global__ __launch_bounds__(64 * PW) void k_tasks(DMRG_TASK_ARGS) {
     extern __shared__ __align__(16) double smem_tasks[];
-    tasks_run<PREC, MODE, NS>(DMRG_TASK_PASS);
+    tasks_run<PREC, MODE, 2>(DMRG_TASK_PASS);
 }
 template <int PREC, int MODE>
 __global__ __launch_bounds__(64 * PW) __attribute__((amdgpu_waves_per_eu(2))) void k_tasks_w2(DMRG_TASK_ARGS) {
@@ -1054,7 +994,7 @@ struct DiagLds {
 };
 
 // out = sum_d c_d vl[r sl] vr[c sr] over each task's diagonal terms, for
-// every element of the task's tile (at most 1024 elements: 4 per thread).
+// every element of the task's tile, 1024 elements at a time (4 per thread).
 // The terms are staged in LDS first, so the slice loads of several terms are
 // in flight together; each element sums its terms in list order.
 __global__ __launch_bounds__(256) void k_diag_terms(const Task *__restrict__ tasks, int ntask,
@@ -1065,45 +1005,47 @@ __global__ __launch_bounds__(256) void k_diag_terms(const Task *__restrict__ tas
         const Task tk = tasks[t];
         const int cnt = tk.m * tk.n;
         if (cnt <= 0) continue;
-        int64_t rr[4], cc[4];
-        double acc[4];
+        for (int e0 = 0; e0 < cnt; e0 += 1024) {
+            int64_t rr[4], cc[4];
+            double acc[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = min((int)threadIdx.x + 256 * q, cnt - 1);
-            rr[q] = tk.row0 + e / tk.n;
-            cc[q] = tk.col0 + e % tk.n;
-            acc[q] = 0.0;
-        }
-        for (int d0 = tk.diag_begin; d0 < tk.diag_end; d0 += DIAG_LDS) {
-            const int nt = min(DIAG_LDS, tk.diag_end - d0);
-            __syncthreads();  // the previous terms are no longer read
-            if ((int)threadIdx.x < nt) {
-                const DiagTerm dt = diags[d0 + threadIdx.x];
-                D.vl[threadIdx.x] = (const double *)(uintptr_t)dt.vl;
-                D.vr[threadIdx.x] = (const double *)(uintptr_t)dt.vr;
-                D.c[threadIdx.x] = coef[dt.coef] * dt.w;
-                D.sl[threadIdx.x] = dt.sl;
-                D.sr[threadIdx.x] = dt.sr;
+            for (int q = 0; q < 4; ++q) {
+                const int e = min(e0 + (int)threadIdx.x + 256 * q, cnt - 1);
+                rr[q] = tk.row0 + e / tk.n;
+                cc[q] = tk.col0 + e % tk.n;
+                acc[q] = 0.0;
             }
-            __syncthreads();
+            for (int d0 = tk.diag_begin; d0 < tk.diag_end; d0 += DIAG_LDS) {
+                const int nt = min(DIAG_LDS, tk.diag_end - d0);
+                __syncthreads();  // the previous terms are no longer read
+                if ((int)threadIdx.x < nt) {
+                    const DiagTerm dt = diags[d0 + threadIdx.x];
+                    D.vl[threadIdx.x] = (const double *)(uintptr_t)dt.vl;
+                    D.vr[threadIdx.x] = (const double *)(uintptr_t)dt.vr;
+                    D.c[threadIdx.x] = coef[dt.coef] * dt.w;
+                    D.sl[threadIdx.x] = dt.sl;
+                    D.sr[threadIdx.x] = dt.sr;
+                }
+                __syncthreads();
 #pragma unroll 4
-            for (int d = 0; d < nt; ++d) {
-                const double *vl = D.vl[d], *vr = D.vr[d];
-                const double c = D.c[d];
-                const int sl = D.sl[d], sr = D.sr[d];
+                for (int d = 0; d < nt; ++d) {
+                    const double *vl = D.vl[d], *vr = D.vr[d];
+                    const double c = D.c[d];
+                    const int sl = D.sl[d], sr = D.sr[d];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    double w = c;
-                    if (vl) w *= vl[rr[q] * sl];
-                    if (vr) w *= vr[cc[q] * sr];
-                    acc[q] += w;
+                    for (int q = 0; q < 4; ++q) {
+                        double w = c;
+                        if (vl) w *= vl[rr[q] * sl];
+                        if (vr) w *= vr[cc[q] * sr];
+                        acc[q] += w;
+                    }
                 }
             }
-        }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = threadIdx.x + 256 * q;
-            if (e < cnt) out[tk.c_off + rr[q] * tk.ldc + cc[q]] = acc[q];
+            for (int q = 0; q < 4; ++q) {
+                const int e = e0 + threadIdx.x + 256 * q;
+                if (e < cnt) out[tk.c_off + rr[q] * tk.ldc + cc[q]] = acc[q];
+            }
         }
     }
 }
@@ -1141,23 +1083,16 @@ dmrg_status launch_convert_jobs(const ConvJob *jobs, int njob, int prec, hipStre
 
 static dim3 task_grid(int ntask) { return dim3(std::min(ntask, TASK_GRID_MAX)); }
 
-// k_tasks<PREC, MODE, NS> launch with the pass list's sub-tile count
+// Task kernel launch with the pass list's sub-tile count (FP64 lists with
+// tiles wider than 16 run on tiles.hip)
 template <int PREC, int MODE, class... Args>
 static void launch_tasks(const Lists &l, size_t lds, hipStream_t s, Args... args) {
-    if constexpr (MODE != 2) {
-        if (l.ns == 1)
-            hipLaunchKernelGGL((k_tasks_w2<PREC, MODE>), task_grid(l.ntask), dim3(64 * PW), lds, s, l.tasks,
-                               l.ntask, args...);
-        else
-            hipLaunchKernelGGL((k_tasks<PREC, MODE, 2>), task_grid(l.ntask), dim3(64 * PW), lds, s, l.tasks,
-                               l.ntask, args...);
-    } else {
-        if (l.ns == 1)
-            hipLaunchKernelGGL((k_tasks<PREC, MODE, 1>), task_grid(l.ntask), dim3(64 * PW), lds, s, l.tasks,
-                               l.ntask, args...);
-        else
-            hipLaunchKernelGGL((k_tasks<PREC, MODE, 2>), task_grid(l.ntask), dim3(64 * PW), lds, s, l.tasks,
-                               l.ntask, args...);
+    if (PREC == DMRG_F64 || l.ns == 1) {
+        hipLaunchKernelGGL((k_tasks_w2<PREC, MODE>), task_grid(l.ntask), dim3(64 * PW), lds, s, l.tasks, l.ntask,
+                           args...);
+    } else if constexpr (PREC != DMRG_F64) {
+        hipLaunchKernelGGL((k_tasks<PREC, MODE>), task_grid(l.ntask), dim3(64 * PW), lds, s, l.tasks, l.ntask,
+                           args...);
     }
 }
 
@@ -1166,13 +1101,11 @@ static dmrg_status run_pass(const PassSet &ps, const double *coef, const double 
                             hipStream_t s, const int32_t *mask, const double *dfold, const RayArgs *ray) {
     if (ps.stageA.ntask)
         launch_tasks<PREC, 0>(ps.stageA, TASK_LDS, s, (const Seg *)ps.segs, (const DiagTerm *)ps.diags, in,
-                              (const void *)tmp, tmp, coef, (const double *)nullptr, (double *)nullptr, mask,
-                              (const double *)nullptr, RayArgs{});
+                              (const void *)tmp, tmp, coef, mask, (const double *)nullptr, RayArgs{});
     if (ps.stageB.ntask) {
         const RayArgs ra = ray ? *ray : RayArgs{};
         launch_tasks<PREC, 1>(ps.stageB, TASK_LDS, s, (const Seg *)ps.segs, (const DiagTerm *)ps.diags, in,
-                              (const void *)tmp, (void *)out, coef, (const double *)nullptr, (double *)nullptr, mask,
-                              dfold, ra);
+                              (const void *)tmp, (void *)out, coef, mask, dfold, ra);
     }
     DMRG_HIP(hipGetLastError());
     return DMRG_OK;
@@ -1180,6 +1113,8 @@ static dmrg_status run_pass(const PassSet &ps, const double *coef, const double 
 
 dmrg_status launch_project(dmrg_plan *plan, int slot, const double *coef, const double *in, double *out,
                            hipStream_t s, const int32_t *mask, const double *dfold, const RayArgs *ray) {
+    if (slot == 0 && plan->fwd[0].wide)
+        return launch_tiles(plan->fwd[0], coef, in, (double *)plan->d_tmp, out, s, mask, dfold, ray);
     if (slot == 0) return run_pass<DMRG_F64>(plan->fwd[0], coef, in, plan->d_tmp, out, s, mask, dfold, ray);
     if (plan->prec == DMRG_F32)
         return run_pass<DMRG_F32>(plan->fwd[1], coef, in, plan->d_tmp, out, s, mask, dfold, ray);
@@ -1187,7 +1122,7 @@ dmrg_status launch_project(dmrg_plan *plan, int slot, const double *coef, const 
 }
 
 dmrg_status launch_adjoint(dmrg_plan *plan, const double *coef, const double *in, double *out, hipStream_t s) {
-    return run_pass<DMRG_F64>(plan->adj[0], coef, in, plan->d_tmp, out, s, nullptr, nullptr, nullptr);
+    return launch_tiles(plan->adj[0], coef, in, (double *)plan->d_tmp, out, s, nullptr, nullptr, nullptr);
 }
 
 dmrg_status launch_diag_fold(dmrg_plan *plan, int slot, const double *coef, double *out, hipStream_t s) {
@@ -1199,17 +1134,15 @@ dmrg_status launch_diag_fold(dmrg_plan *plan, int slot, const double *coef, doub
     return DMRG_OK;
 }
 
-dmrg_status launch_gcoef(dmrg_plan *plan, const double *psi, const double *gbar, double *gcoef, hipStream_t s) {
-    const PassSet &ps = plan->fwd[0];
-    if (ps.stageA.ntask)
-        launch_tasks<DMRG_F64, 0>(ps.stageA, TASK_LDS, s, (const Seg *)ps.segs, (const DiagTerm *)ps.diags, psi,
-                                  (const void *)plan->d_tmp, (void *)plan->d_tmp, (const double *)nullptr,
-                                  (const double *)nullptr, (double *)nullptr, (const int32_t *)nullptr,
-                                  (const double *)nullptr, RayArgs{});
-    if (ps.stageB.ntask)
-        launch_tasks<DMRG_F64, 2>(ps.stageB, TASK_LDS, s, (const Seg *)ps.segs, (const DiagTerm *)ps.diags, psi,
-                                  (const void *)plan->d_tmp, (void *)nullptr, (const double *)nullptr, gbar,
-                                  plan->d_partials, (const int32_t *)nullptr, (const double *)nullptr, RayArgs{});
+dmrg_status launch_gcoef(dmrg_plan *plan, const double *coef, const double *psi, const double *gbar, double *gpsi,
+                         double *gcoef, hipStream_t s) {
+    // gcoef_k = <gbar, T_k psi> = <psi, T_k^T gbar>: the segment products the
+    // adjoint pass forms anyway, each multiplied by its tile of psi
+    if (plan->d_partials)
+        DMRG_TRY(launch_tiles(plan->adj[0], coef, gbar, (double *)plan->d_tmp, gpsi, s, nullptr, nullptr, nullptr,
+                              psi, plan->d_partials));
+    else if (gpsi)
+        DMRG_TRY(launch_adjoint(plan, coef, gbar, gpsi, s));
     if (plan->nterm_total)
         hipLaunchKernelGGL(k_reduce_terms, dim3(plan->nterm_total), dim3(64), 0, s, plan->d_term_ptr,
                            plan->d_term_ent, (const double *)plan->d_partials, gcoef, plan->nterm_total);
@@ -1230,7 +1163,7 @@ dmrg_status launch_diagonal(dmrg_plan *plan, const double *coef, double *diag, h
 dmrg_status launch_project_multi(dmrg_plan *plan, const double *coef, const double *in, int64_t in_stride,
                                  double *out, int64_t out_stride, const int32_t *vmask, hipStream_t s) {
     const PassSet &ps = plan->fwd[0];
-    if (ps.stageA.ns != 1 || ps.stageB.ns != 1) {
+    if (ps.wide) {
         for (int v = 0; v < NVEC; ++v)
             DMRG_TRY(launch_project(plan, 0, coef, in + v * in_stride, out + v * out_stride, s,
                                     vmask ? vmask + v : nullptr));
@@ -1302,8 +1235,8 @@ dmrg_status dmrg_project_backward(dmrg_plan *plan, const double *coef, const dou
     if (gpsi && gpsi == gbar) return set_error(DMRG_E_INVALID_ARG, "gpsi and gbar must not overlap");
     DMRG_TRY(check_device(plan));
     hipStream_t s = (hipStream_t)stream;
-    if (gcoef) DMRG_TRY(launch_gcoef(plan, psi, gbar, gcoef, s));
-    if (gpsi) DMRG_TRY(launch_adjoint(plan, coef, gbar, gpsi, s));
+    if (gcoef) return launch_gcoef(plan, coef, psi, gbar, gpsi, gcoef, s);
+    if (gpsi) return launch_adjoint(plan, coef, gbar, gpsi, s);
     return DMRG_OK;
 }
 
