@@ -34,7 +34,9 @@ void clear_error();
 // Pointer to device memory.  An address that comes out of a descriptor is a
 // generic pointer to the compiler, whose (flat) loads can only be waited for all
 // at once; a load through this type can be in flight behind later ones.
-typedef const __attribute__((address_space(1))) double *gptr;
+template <class T>
+using gptr_of = const __attribute__((address_space(1))) T *;
+typedef gptr_of<double> gptr;
 __host__ __device__ inline gptr as_global(uint64_t a) { return (gptr)(uintptr_t)a; }
 
 // Where a GEMM operand lives.
@@ -155,6 +157,7 @@ struct Lists {  // device task lists of one pass
     Task *tasks = nullptr;
     int32_t ntask = 0;
     int32_t ns = 1;  // 16 x 16 sub-tiles per tile side: 1 when every tile fits 16 x 16, else 2
+    int32_t stride = 0, dstride = 0;  // descriptors of consecutive tiles' segments / diagonal terms, 0: not packed
     Split *splits = nullptr;  // passes of 32-wide tiles: [ntask * TWA] (stage A) or [ntask * TWB]
 };
 
@@ -165,6 +168,7 @@ struct PassSet {  // everything one projection direction needs in one precision
     DiagTerm *diags = nullptr;
     int32_t nseg = 0, ndiag = 0;
     int64_t tmp_elems = 0;  // intermediate buffer length (elements)
+    bool small = true;      // no block of 2^28 elements or more (32-bit byte offsets inside a block)
     int32_t wide = 0;       // side of the pass's tiles in tiles.hip, 0: the kernels of project.hip
 };
 
@@ -273,6 +277,9 @@ dmrg_status launch_diagonal(dmrg_plan *plan, const double *coef, double *diag, h
 constexpr int PROJ_NVEC = 4;
 dmrg_status launch_project_multi(dmrg_plan *plan, const double *coef, const double *in, int64_t in_stride,
                                  double *out, int64_t out_stride, const int32_t *vmask, hipStream_t s);
+// fused.hip: output tiles of a pass whose tiles all fit 16 x 16 (F64 or F32)
+dmrg_status launch_fused(const PassSet &ps, int prec, const double *coef, const double *in, const void *tmp,
+                         double *out, hipStream_t s, const int32_t *mask, const double *dfold, const RayArgs *ray);
 // tiles.hip: a wide FP64 pass (both stages).  xg, partials: adjoint passes that
 // also form the coefficient-gradient partials <xg, segment product> (out may be null then)
 dmrg_status launch_tiles(const PassSet &ps, const double *coef, const double *in, double *tmp, double *out,

@@ -60,4 +60,11 @@ __device__ __forceinline__ double wave_min(double v) {
     return fmin(fmin(readlane_f64(v, 0), readlane_f64(v, 16)), fmin(readlane_f64(v, 32), readlane_f64(v, 48)));
 }
 
+// A value whose dependent addresses are not worth registers across a loop: the
+// compiler neither hoists nor keeps what is computed from the result.
+__device__ __forceinline__ int rare(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 }  // namespace dmrg

@@ -248,6 +248,7 @@ struct HostPass {
     std::vector<Task> A, B;
     std::vector<Split> splitA, splitB;  // wide passes
     int wide = 0;                       // see PassSet
+    bool small = true;
     std::vector<Seg> segs;
     std::vector<DiagTerm> diags;
     int64_t tmp = 0;
@@ -355,6 +356,43 @@ static void order_for_xcds(std::vector<Task> &v) {
     v.swap(o);
 }
 
+// Descriptors of a small pass's output tiles at a fixed stride, so that a tile
+// reads them without waiting for its record (two cold misses in a row, 0.8 us each, become one).  Only where
+// tiles are few enough for that latency to show, and their lists short.
+static void pack_tiles(HostPass &hp, int32_t *stride, int32_t *dstride) {
+    constexpr size_t MAX_TILES = 1024;
+    constexpr int MAX_SEGS = 12, MAX_DIAGS = 16;
+    *stride = *dstride = 0;
+    int ns = 0, nd = 0;
+    for (const Task &t : hp.B) {
+        ns = std::max(ns, t.seg_end - t.seg_begin);
+        nd = std::max(nd, t.diag_end - t.diag_begin);
+    }
+    if (hp.wide || hp.B.empty() || hp.B.size() > MAX_TILES || ns > MAX_SEGS || nd > MAX_DIAGS) return;
+    std::vector<Seg> segs(hp.B.size() * ns);
+    std::vector<DiagTerm> diags(hp.B.size() * nd);
+    for (size_t i = 0; i < hp.B.size(); ++i) {
+        Task &t = hp.B[i];
+        const int s0 = (int)(i * ns), d0 = (int)(i * nd);
+        std::copy(hp.segs.begin() + t.seg_begin, hp.segs.begin() + t.seg_end, segs.begin() + s0);
+        std::copy(hp.diags.begin() + t.diag_begin, hp.diags.begin() + t.diag_end, diags.begin() + d0);
+        t.seg_end += s0 - t.seg_begin;
+        t.seg_begin = s0;
+        t.diag_end += d0 - t.diag_begin;
+        t.diag_begin = d0;
+    }
+    for (Task &t : hp.A) {
+        const int s0 = (int)segs.size();
+        segs.insert(segs.end(), hp.segs.begin() + t.seg_begin, hp.segs.begin() + t.seg_end);
+        t.seg_end += s0 - t.seg_begin;
+        t.seg_begin = s0;
+    }
+    hp.segs.swap(segs);
+    hp.diags.swap(diags);
+    *stride = ns;
+    *dstride = nd;
+}
+
 // The TW runs of every tile of a wide stage, in task order.  With slots, the
 // coefficient-gradient partials are numbered too: one per run and segment,
 // then one per diagonal term of the tile (Task::part0), listed per term.
@@ -438,8 +476,11 @@ static void build_pass(const dmrg_plan *plan, bool adjoint, LowStore *low, uint6
     // fuse into one launch) keep the kernels of project.hip.  A tile table of one
     // class asks for one tile size whatever else is in the plan (a member's result is
     // then the same bits alone and in a batch): no 64 x 64 tiles there.
+    for (const Geo &g : plan->out_geo) hp.small = hp.small && g.rows * g.ld < (int64_t)1 << 28;
+    for (const Record &rc : plan->records)
+        for (const OpBlock *b : {&rc.a, &rc.b}) hp.small = hp.small && b->rows * b->cols < (int64_t)1 << 28;
     if (!low) {
-        hp.wide = adjoint ? 32 : 0;
+        hp.wide = adjoint || !hp.small ? 32 : 0;
         for (const Geo &g : plan->out_geo)
             if (tile_for(g.rows, g.cols) > 16) hp.wide = 32;
         int64_t n64 = 0;
@@ -700,7 +741,8 @@ static dmrg_status upload(dmrg_plan *plan, const std::vector<T> &v, T **dst, hip
     return DMRG_OK;
 }
 
-static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, hipStream_t s) {
+static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, bool pack, hipStream_t s) {
+    if (pack) pack_tiles(hp, &ps.stageB.stride, &ps.stageB.dstride);
     // member-contiguous rows for the per-tile Rayleigh partials of stage B
     std::vector<int32_t> begin(plan->nprob + 1, 0), next;
     for (const Task &t : hp.B) begin[t.member + 1] += 1;
@@ -719,6 +761,7 @@ static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, hipSt
     for (const Task &t : hp.B)
         if (t.m > 16 || t.n > 16) ps.stageB.ns = 2;
     ps.wide = hp.wide;
+    ps.small = hp.small;
     DMRG_TRY(upload(plan, hp.splitA, &ps.stageA.splits, s));
     DMRG_TRY(upload(plan, hp.splitB, &ps.stageB.splits, s));
     ps.nseg = (int32_t)hp.segs.size();
@@ -936,8 +979,8 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
             plan->d_partials = (double *)q;
         }
     }
-    DMRG_TRY(upload_pass(plan, f64, plan->fwd[0], stream));
-    DMRG_TRY(upload_pass(plan, a64, plan->adj[0], stream));
+    DMRG_TRY(upload_pass(plan, f64, plan->fwd[0], true, stream));
+    DMRG_TRY(upload_pass(plan, a64, plan->adj[0], false, stream));
     int64_t tmp = std::max(f64.tmp, a64.tmp);
 
     // ---- low-precision forward pass with converted operator copies
@@ -961,7 +1004,7 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
         ConvJob *d_jobs = nullptr;
         DMRG_TRY(upload(plan, jobs, &d_jobs, stream));
         DMRG_TRY(launch_convert_jobs(d_jobs, (int)jobs.size(), prec, stream));
-        DMRG_TRY(upload_pass(plan, lo2, plan->fwd[1], stream));
+        DMRG_TRY(upload_pass(plan, lo2, plan->fwd[1], prec == DMRG_F32, stream));
         tmp = std::max(tmp, lo2.tmp);
     }
     plan->tmp_bytes = std::max<int64_t>(tmp, 1) * 8;

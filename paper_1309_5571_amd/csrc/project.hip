@@ -138,7 +138,7 @@ __device__ __forceinline__ void load_p(typename Tr<PREC>::val_t (&v)[Tr<PREC>::K
                                        bool row_ok, int k0, int K, double scale) {
     typedef Tr<PREC> T;
     if (PIN) {
-        const double *P = in + s.p;
+        const gptr P = (gptr)in + s.p;
 #pragma unroll
         for (int j = 0; j < T::KPL; ++j) {
             int k = k0 + j * T::template kstep<ST>();
@@ -147,43 +147,13 @@ __device__ __forceinline__ void load_p(typename Tr<PREC>::val_t (&v)[Tr<PREC>::K
             v[j] = T::from_in(x * scale);
         }
     } else {
-        const typename T::store_t *P = (s.pkind == OPD_ABS)
-                                           ? (const typename T::store_t *)(uintptr_t)s.p
-                                           : (const typename T::store_t *)tmp + s.p;
+        typedef gptr_of<typename T::store_t> S;
+        const S P = (s.pkind == OPD_ABS) ? (S)(uintptr_t)s.p : (S)tmp + s.p;
 #pragma unroll
         for (int j = 0; j < T::KPL; ++j) {
             int k = k0 + j * T::template kstep<ST>();
             typename T::store_t x = 0;
             if (row_ok && k < K) x = PT ? P[(int64_t)k * s.ldp + row] : P[(int64_t)row * s.ldp + k];
-            v[j] = T::from_store(x);
-        }
-    }
-}
-
-// Q fragment: column col, k = k0 + kstep j (k0: the lane's kbase)
-template <int PREC, bool QIN, bool QT, bool ST = false>
-__device__ __forceinline__ void load_q(typename Tr<PREC>::val_t (&v)[Tr<PREC>::KPL], const Seg &s,
-                                       const double *__restrict__ in, const void *__restrict__ tmp, int col,
-                                       bool col_ok, int k0, int K, double scale) {
-    typedef Tr<PREC> T;
-    if (QIN) {
-        const double *Q = in + s.q;
-#pragma unroll
-        for (int j = 0; j < T::KPL; ++j) {
-            int k = k0 + j * T::template kstep<ST>();
-            double x = 0.0;
-            if (col_ok && k < K) x = QT ? Q[(int64_t)col * s.ldq + k] : Q[(int64_t)k * s.ldq + col];
-            v[j] = T::from_in(x * scale);
-        }
-    } else {
-        const typename T::store_t *Q = (s.qkind == OPD_ABS)
-                                           ? (const typename T::store_t *)(uintptr_t)s.q
-                                           : (const typename T::store_t *)tmp + s.q;
-#pragma unroll
-        for (int j = 0; j < T::KPL; ++j) {
-            int k = k0 + j * T::template kstep<ST>();
-            typename T::store_t x = 0;
-            if (col_ok && k < K) x = QT ? Q[(int64_t)col * s.ldq + k] : Q[(int64_t)k * s.ldq + col];
             v[j] = T::from_store(x);
         }
     }
@@ -217,7 +187,7 @@ __device__ __forceinline__ void cvt_frag(typename Tr<PREC>::val_t (&v)[Tr<PREC>:
 // at base + off, leading dimension ld, transposed when TR.
 template <int PREC, bool IN, bool TR, bool ST>
 __device__ __forceinline__ void load_raw(typename RawT<PREC, IN>::type (&v)[Tr<PREC>::KPL],
-                                         const typename RawT<PREC, IN>::type *__restrict__ B, int ld, int rc,
+                                         gptr_of<typename RawT<PREC, IN>::type> B, int ld, int rc,
                                          bool rc_ok, int k0, int K) {
     typedef typename RawT<PREC, IN>::type R;
 #pragma unroll
@@ -232,7 +202,7 @@ __device__ __forceinline__ void load_raw(typename RawT<PREC, IN>::type (&v)[Tr<P
 // to its element (0, 0) and the values zeroed after every load has been issued.
 template <int PREC, bool IN, bool TR, bool ST>
 __device__ __forceinline__ void load_raw_u(typename RawT<PREC, IN>::type (&v)[Tr<PREC>::KPL],
-                                           const typename RawT<PREC, IN>::type *__restrict__ B, int ld, int rc,
+                                           gptr_of<typename RawT<PREC, IN>::type> B, int ld, int rc,
                                            bool rc_ok, int k0, int K) {
     typedef typename RawT<PREC, IN>::type R;
 #pragma unroll
@@ -249,14 +219,14 @@ __device__ __forceinline__ void load_raw_u(typename RawT<PREC, IN>::type (&v)[Tr
     }
 }
 template <int PREC, bool IN>
-__device__ __forceinline__ const typename RawT<PREC, IN>::type *raw_base(const double *__restrict__ in,
-                                                                         const void *__restrict__ tmp, uint64_t a,
-                                                                         int16_t kind) {
-    typedef typename RawT<PREC, IN>::type R;
+__device__ __forceinline__ gptr_of<typename RawT<PREC, IN>::type> raw_base(const double *__restrict__ in,
+                                                                           const void *__restrict__ tmp, uint64_t a,
+                                                                           int32_t kind) {
+    typedef gptr_of<typename RawT<PREC, IN>::type> R;
     if constexpr (IN)
-        return in + a;
+        return (R)in + a;
     else
-        return (kind == OPD_ABS) ? (const R *)(uintptr_t)a : (const R *)tmp + a;
+        return (kind == OPD_ABS) ? (R)(uintptr_t)a : (R)tmp + a;
 }
 
 constexpr int PW = 4;            // wavefronts per workgroup
@@ -295,13 +265,12 @@ __device__ __forceinline__ void item_gemm(typename Tr<PREC>::acc_t (&acc)[2][2],
         int c = t * 16 + r16;
         qok[t] = c < tk.n;
         qcol[t] = tk.col0 + (qok[t] ? c : 0);
-        if (PIN && s.pscale && pok[t]) ps[t] = ((const double *)(uintptr_t)s.pscale)[prow[t]];
-        if (QIN && s.qscale && qok[t]) qs[t] = ((const double *)(uintptr_t)s.qscale)[qcol[t]];
+        if (PIN && s.pscale && pok[t]) ps[t] = as_global(s.pscale)[prow[t]];
+        if (QIN && s.qscale && qok[t]) qs[t] = as_global(s.qscale)[qcol[t]];
     }
     if constexpr (PREC == DMRG_F64) {
         typename T::val_t pv[NS][NKB][T::KPL], qv[NS][NKB][T::KPL];
-        const double *P = raw_base<PREC, PIN>(in, tmp, s.p, s.pkind);
-        const double *Q = raw_base<PREC, QIN>(in, tmp, s.q, s.qkind);
+        const gptr P = raw_base<PREC, PIN>(in, tmp, s.p, s.pkind), Q = raw_base<PREC, QIN>(in, tmp, s.q, s.qkind);
 #pragma unroll
         for (int b = 0; b < NKB; ++b) {
             const int kk = T::template kbase<false>(k0 + b * KB, g);
@@ -388,39 +357,30 @@ __device__ __forceinline__ void fused_item(typename Tr<PREC>::acc_t (&acc)[2][2]
     for (int k0 = 0; k0 < s.K; k0 += KB) {
         typename T::val_t pv[T::KPL], qv[4][T::KPL];
         const int kk = T::template kbase<true>(k0, g);
-        if constexpr (T::KPL == 4 && PREC != DMRG_F64) {  // FP32: raw FP64 input, converted at the MFMA
+        if constexpr (T::KPL == 4) {  // FP32: raw FP64 input, converted at the MFMA
             double qr[4][T::KPL];
             load_p<PREC, false, false, true>(pv, s, in, nullptr, prow, pok, kk, s.K, 1.0);
 #pragma unroll
             for (int cs = 0; cs < 4; ++cs) {
                 const int col = cs * 16 + r16;
                 if (cs < ncs)
-                    load_raw<PREC, true, true, true>(qr[cs], in + s.q, s.ldq, col < s.K2 ? col : 0, col < s.K2, kk,
+                    load_raw<PREC, true, true, true>(qr[cs], (gptr)in + s.q, s.ldq, col < s.K2 ? col : 0, col < s.K2, kk,
                                                      s.K);
             }
 #pragma unroll
             for (int cs = 0; cs < 4; ++cs)
                 if (cs < ncs) cvt_frag<PREC, true>(qv[cs], qr[cs], 1.0);
-        } else if constexpr (PREC != DMRG_F64) {  // BF16: unconditional loads, one sub-tile at a time
+        } else {  // BF16: unconditional loads, one sub-tile at a time
             load_p<PREC, false, false, true>(pv, s, in, nullptr, prow, pok, kk, s.K, 1.0);
 #pragma unroll
             for (int cs = 0; cs < 4; ++cs) {
                 const int col = cs * 16 + r16;
                 if (cs < ncs) {
                     double qr[T::KPL];
-                    load_raw_u<PREC, true, true, true>(qr, in + s.q, s.ldq, col < s.K2 ? col : 0, col < s.K2, kk,
+                    load_raw_u<PREC, true, true, true>(qr, (gptr)in + s.q, s.ldq, col < s.K2 ? col : 0, col < s.K2, kk,
                                                        s.K);
                     cvt_frag<PREC, true>(qv[cs], qr, 1.0);
                 }
-            }
-        } else {
-            load_p<PREC, false, false, true>(pv, s, in, nullptr, prow, pok, kk, s.K, 1.0);
-#pragma unroll
-            for (int cs = 0; cs < 4; ++cs) {
-                const int col = cs * 16 + r16;
-                if (cs < ncs)
-                    load_q<PREC, true, false, true>(qv[cs], s, in, nullptr, col < s.K2 ? col : 0, col < s.K2, kk,
-                                                    s.K, 1.0);
             }
         }
 #pragma unroll
@@ -434,7 +394,7 @@ __device__ __forceinline__ void fused_item(typename Tr<PREC>::acc_t (&acc)[2][2]
             for (int v = 0; v < 4; ++v) tl[T::row(g, v) * 64 + cs * 16 + r16] = (double)a1[cs][v];
         }
     wave_lds_sync();
-    const typename T::store_t *R = (const typename T::store_t *)(uintptr_t)s.r;
+    const gptr_of<typename T::store_t> R = (gptr_of<typename T::store_t>)(uintptr_t)s.r;
     for (int k0 = 0; k0 < s.K2; k0 += KB) {
         typename T::val_t pv[T::KPL], qv[NS][T::KPL];
         const int kk = T::template kbase<true>(k0, g);
@@ -530,8 +490,7 @@ __device__ __forceinline__ void copy_item(double (&v)[NS][NS][4], const Seg &s, 
                                           const double *__restrict__ in) {
     const int lane = threadIdx.x & 63;
     const int r16 = lane & 15, g = lane >> 4;
-    const double *X = in + s.q;
-    const double *vl = (const double *)(uintptr_t)s.pscale, *vr = (const double *)(uintptr_t)s.qscale;
+    const gptr X = (gptr)in + s.q, vl = as_global(s.pscale), vr = as_global(s.qscale);
 #pragma unroll
     for (int a = 0; a < NS; ++a)
 #pragma unroll
@@ -743,9 +702,7 @@ __device__ __forceinline__ void fused_item_nv(v4d (&acc)[NV], const Seg &s, cons
     const int row = tk.row0 + (rok ? c : 0);
     const bool cok = c < tk.n;
     const int col = tk.col0 + (cok ? c : 0);
-    const double *A = (const double *)(uintptr_t)s.p;
-    const double *B = (const double *)(uintptr_t)s.r;
-    const double *X = in + s.q;
+    const gptr A = as_global(s.p), B = as_global(s.r), X = (gptr)in + s.q;
     const int ncs = (s.K2 + 15) >> 4;
     for (int cs = 0; cs < ncs; ++cs) {
         v4d t1[NV];
@@ -803,13 +760,13 @@ __device__ __forceinline__ void item_gemm_nv(v4d (&acc)[NVEC], const Seg &s, con
     const bool pok = r16 < tk.m, qok = r16 < tk.n;
     const int prow = tk.row0 + (pok ? r16 : 0), qcol = tk.col0 + (qok ? r16 : 0);
     const bool pv = s.pkind != OPD_ABS;  // which operand depends on the vector
-    const double *P = (s.pkind == OPD_ABS) ? (const double *)(uintptr_t)s.p : (PIN ? in : tmp) + s.p;
-    const double *Q = (s.qkind == OPD_ABS) ? (const double *)(uintptr_t)s.q : (QIN ? in : tmp) + s.q;
+    const gptr P = (s.pkind == OPD_ABS) ? as_global(s.p) : (gptr)(PIN ? in : tmp) + s.p;
+    const gptr Q = (s.qkind == OPD_ABS) ? as_global(s.q) : (gptr)(QIN ? in : tmp) + s.q;
     const int64_t pstr = pv ? (PIN ? ma.in_stride : ma.tmp_stride) : 0;
     const int64_t qstr = pv ? 0 : (QIN ? ma.in_stride : ma.tmp_stride);
     double ps = 1.0, qs = 1.0;
-    if (PIN && s.pscale && pok) ps = ((const double *)(uintptr_t)s.pscale)[prow];
-    if (QIN && s.qscale && qok) qs = ((const double *)(uintptr_t)s.qscale)[qcol];
+    if (PIN && s.pscale && pok) ps = as_global(s.pscale)[prow];
+    if (QIN && s.qscale && qok) qs = as_global(s.qscale)[qcol];
     double sh[NKB][4], pvec[NVEC][NKB][4];  // the shared operand, the per-vector one
 #pragma unroll
     for (int b = 0; b < NKB; ++b) {
@@ -988,7 +945,7 @@ __global__ __launch_bounds__(64) void k_reduce_terms(const int32_t *__restrict__
 // (null = ones), strides and coefficients.
 constexpr int DIAG_LDS = 64;
 struct DiagLds {
-    const double *vl[DIAG_LDS], *vr[DIAG_LDS];
+    gptr vl[DIAG_LDS], vr[DIAG_LDS];
     double c[DIAG_LDS];
     int sl[DIAG_LDS], sr[DIAG_LDS];
 };
@@ -1020,8 +977,8 @@ __global__ __launch_bounds__(256) void k_diag_terms(const Task *__restrict__ tas
                 __syncthreads();  // the previous terms are no longer read
                 if ((int)threadIdx.x < nt) {
                     const DiagTerm dt = diags[d0 + threadIdx.x];
-                    D.vl[threadIdx.x] = (const double *)(uintptr_t)dt.vl;
-                    D.vr[threadIdx.x] = (const double *)(uintptr_t)dt.vr;
+                    D.vl[threadIdx.x] = as_global(dt.vl);
+                    D.vr[threadIdx.x] = as_global(dt.vr);
                     D.c[threadIdx.x] = coef[dt.coef] * dt.w;
                     D.sl[threadIdx.x] = dt.sl;
                     D.sr[threadIdx.x] = dt.sr;
@@ -1029,7 +986,7 @@ __global__ __launch_bounds__(256) void k_diag_terms(const Task *__restrict__ tas
                 __syncthreads();
 #pragma unroll 4
                 for (int d = 0; d < nt; ++d) {
-                    const double *vl = D.vl[d], *vr = D.vr[d];
+                    const gptr vl = D.vl[d], vr = D.vr[d];
                     const double c = D.c[d];
                     const int sl = D.sl[d], sr = D.sr[d];
 #pragma unroll
@@ -1083,8 +1040,9 @@ dmrg_status launch_convert_jobs(const ConvJob *jobs, int njob, int prec, hipStre
 
 static dim3 task_grid(int ntask) { return dim3(std::min(ntask, TASK_GRID_MAX)); }
 
-// Task kernel launch with the pass list's sub-tile count (FP64 lists with
-// tiles wider than 16 run on tiles.hip)
+// Task kernel launch with the pass list's sub-tile count.  FP64 passes come
+// here for the intermediates of all-16 plans only (output tiles run on
+// fused.hip, wider tiles on tiles.hip), FP32 ones unless their tiles fit 16 x 16.
 template <int PREC, int MODE, class... Args>
 static void launch_tasks(const Lists &l, size_t lds, hipStream_t s, Args... args) {
     if (PREC == DMRG_F64 || l.ns == 1) {
@@ -1102,7 +1060,9 @@ static dmrg_status run_pass(const PassSet &ps, const double *coef, const double 
     if (ps.stageA.ntask)
         launch_tasks<PREC, 0>(ps.stageA, TASK_LDS, s, (const Seg *)ps.segs, (const DiagTerm *)ps.diags, in,
                               (const void *)tmp, tmp, coef, mask, (const double *)nullptr, RayArgs{});
-    if (ps.stageB.ntask) {
+    if (PREC == DMRG_F64 || (PREC == DMRG_F32 && ps.stageB.ns == 1 && ps.small))
+        return launch_fused(ps, PREC, coef, in, tmp, out, s, mask, dfold, ray);
+    if constexpr (PREC != DMRG_F64) if (ps.stageB.ntask) {
         const RayArgs ra = ray ? *ray : RayArgs{};
         launch_tasks<PREC, 1>(ps.stageB, TASK_LDS, s, (const Seg *)ps.segs, (const DiagTerm *)ps.diags, in,
                               (const void *)tmp, (void *)out, coef, mask, dfold, ra);

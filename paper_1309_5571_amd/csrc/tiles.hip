@@ -163,13 +163,6 @@ __device__ __forceinline__ uint64_t uni(uint64_t v) {
     return (uint64_t)uni((uint32_t)(v >> 32)) << 32 | uni((uint32_t)v);
 }
 
-// A lane index whose dependent addresses are not worth registers across the
-// item loop (the compiler hoists them out of rare branches otherwise).
-__device__ __forceinline__ int rare(int v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 // Segments whose items are not fetched ahead: contractions shorter than a
 // window, single rows or columns where pairs are needed, rows too long for 32-bit
 // offsets, and copies.

@@ -121,3 +121,27 @@ def test_many_segments_and_copies():
     y = plan.project_raw(_dev(psi)).cpu().numpy()
     ref = l11r.project_sectors(p, psi)
     assert np.linalg.norm(y - ref) <= 1e-12 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("e", range(len(EDGES)))
+def test_fused_edges(e, prec):
+    """16 x 16 tiles: contractions and intermediates around 16, 36 and 64 (one
+    piece, several pieces, two stages), with packed descriptors and tiles
+    without a segment.  FP32 against the accumulation envelope K 2^-24 + 6 u
+    of the exact product magnitudes."""
+    import paper_1309_5571_amd as dm
+    from oracle import precision
+
+    p = _problem(EDGES[e], EDGES[-1 - e], 30 + e)
+    if e == 0:  # only diagonal terms reach some of the tiles
+        p.terms, p.coef = p.terms[[2, 6]], p.coef[[2, 6]]
+    plan = dm.Plan(p, prec=prec, tiles=((1 << 30,), (16,)))
+    psi = np.random.default_rng(e).standard_normal(plan.n)
+    y = plan.project_raw(_dev(psi), prec=prec).cpu().numpy()
+    ref = projection.project_sectors(p, psi)
+    if prec == "f64":
+        assert np.linalg.norm(y - ref) <= 1e-12 * np.linalg.norm(ref)
+    else:
+        env = (precision.max_contraction(p) + 6) * 2.0 ** -24 * np.linalg.norm(precision.project_magnitude(p, psi))
+        assert np.linalg.norm(y - ref) <= env
