@@ -299,8 +299,9 @@ dmrg_status dmrg_diagonal(dmrg_plan *plan, const double *coef, double *diag, voi
  * 5, 12, 13) on column-major V (device FP64, column j at V + j * ldv):
  *  dmrg_gemv_t: s[j] = sum_e V[e, j] x[e], j < k          (s: device [k])
  *  dmrg_gemv_n: y[e] = beta * y[e] + sum_j V[e, j] s[j]    (y: device [n])
- * n <= ldv, 1 <= k <= 64.  Asynchronous.  These are the kernels the
- * Davidson driver uses, exposed for measurement. */
+ * n <= ldv, 1 <= k <= 64.  Asynchronous.  The Davidson driver does the same
+ * sums inside its own kernels; these serve programs that orthogonalize by
+ * themselves, and measurement. */
 dmrg_status dmrg_gemv_t(int64_t n, int32_t k, const double *V, int64_t ldv, const double *x,
                         double *s, void *stream);
 dmrg_status dmrg_gemv_n(int64_t n, int32_t k, const double *V, int64_t ldv, const double *s,

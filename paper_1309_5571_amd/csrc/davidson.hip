@@ -1658,21 +1658,6 @@ static dmrg_status phase_run(dmrg_plan *plan, Phase &P, hipStream_t s, std::vect
 
 using namespace dmrg;
 
-template <int KB>
-__global__ __launch_bounds__(TPB) void k_gemv_n(int64_t n, int k, const double *__restrict__ V, int64_t ldv,
-                                                const double *__restrict__ s, double beta, double *__restrict__ y) {
-    double sv[KB];
-#pragma unroll
-    for (int j = 0; j < KB; ++j) sv[j] = (j < k) ? s[j] : 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * TPB + threadIdx.x; e < n; e += (int64_t)gridDim.x * TPB) {
-        double acc = (beta == 0.0) ? 0.0 : beta * y[e];
-#pragma unroll
-        for (int j = 0; j < KB; ++j)
-            if (j < k) acc += V[(int64_t)j * ldv + e] * sv[j];
-        y[e] = acc;
-    }
-}
-
 // Partials of dmrg_gemv_t: one buffer per (device, stream), kept until the
 // process ends, so calls on different streams never share one.  The map is
 // guarded; a buffer only grows, after its own stream has drained.
@@ -1682,24 +1667,6 @@ struct GemvScratch {
 };
 static std::map<std::pair<int, hipStream_t>, GemvScratch> g_gemv_scratch;
 static std::mutex g_gemv_mutex;
-
-// Both stages of s = V^T x with the partials in part (>= nblk * 64 doubles).
-dmrg_status gemv_t_launch(int64_t n, int32_t k, const double *V, int64_t ldv, const double *x, double *s,
-                                 int nblk, double *part, hipStream_t st) {
-    auto go = [&](auto kb) {
-        constexpr int KB = decltype(kb)::value;
-        hipLaunchKernelGGL(k_gemv_t_part<KB>, dim3(nblk), dim3(TPB), 0, st, n, k, V, ldv, x, part);
-        hipLaunchKernelGGL(k_gemv_t_final<KB>, dim3(1), dim3(TPB), 0, st, nblk, k, (const double *)part, s);
-    };
-    if (k <= 16)
-        go(std::integral_constant<int, 16>{});
-    else if (k <= 32)
-        go(std::integral_constant<int, 32>{});
-    else
-        go(std::integral_constant<int, 64>{});
-    DMRG_HIP(hipGetLastError());
-    return DMRG_OK;
-}
 
 extern "C" {
 
@@ -1848,8 +1815,7 @@ dmrg_status dmrg_gemv_t(int64_t n, int32_t k, const double *V, int64_t ldv, cons
     clear_error();
     if (n < 1 || k < 1 || k > 64 || ldv < n || !V || !x || !s)
         return set_error(DMRG_E_INVALID_ARG, "need n >= 1, 1 <= k <= 64, ldv >= n and non-null pointers");
-    const int nblk = (int)std::min<int64_t>((n + TPB - 1) / TPB, GEMV_PART_BLOCKS);
-    const size_t need = (size_t)nblk * GEMV_PART_COLS * 8;
+    const size_t need = (size_t)gemv_t_blocks(n) * GEMV_PART_COLS * 8;
     int dev = 0;
     DMRG_HIP(hipGetDevice(&dev));
     hipStream_t st = (hipStream_t)stream;
@@ -1868,7 +1834,7 @@ dmrg_status dmrg_gemv_t(int64_t n, int32_t k, const double *V, int64_t ldv, cons
         }
         part = gs.p;
     }
-    return gemv_t_launch(n, k, V, ldv, x, s, nblk, part, st);
+    return gemv_t_launch(n, k, V, ldv, x, s, part, st);
 }
 
 dmrg_status dmrg_gemv_n(int64_t n, int32_t k, const double *V, int64_t ldv, const double *s, double beta,
@@ -1876,20 +1842,7 @@ dmrg_status dmrg_gemv_n(int64_t n, int32_t k, const double *V, int64_t ldv, cons
     clear_error();
     if (n < 1 || k < 1 || k > 64 || ldv < n || !V || !s || !y)
         return set_error(DMRG_E_INVALID_ARG, "need n >= 1, 1 <= k <= 64, ldv >= n and non-null pointers");
-    int nblk = (int)std::min<int64_t>((n + TPB - 1) / TPB, 8192);
-    hipStream_t st = (hipStream_t)stream;
-    auto go = [&](auto kb) {
-        constexpr int KB = decltype(kb)::value;
-        hipLaunchKernelGGL(k_gemv_n<KB>, dim3(nblk), dim3(TPB), 0, st, n, k, V, ldv, s, beta, y);
-    };
-    if (k <= 16)
-        go(std::integral_constant<int, 16>{});
-    else if (k <= 32)
-        go(std::integral_constant<int, 32>{});
-    else
-        go(std::integral_constant<int, 64>{});
-    DMRG_HIP(hipGetLastError());
-    return DMRG_OK;
+    return gemv_n_launch(n, k, V, ldv, s, beta, y, (hipStream_t)stream);
 }
 
 }  // extern "C"

@@ -50,10 +50,10 @@ extern "C" dmrg_status dmrg_gemv_t_noalloc(int64_t n, int32_t k, const double *V
     if (k < 1 || k > GEMV_PART_COLS)
         return set_error(DMRG_E_INVALID_ARG, "k = %d outside 1..%d: the fixed partial-sum buffer holds %d columns", k,
                          GEMV_PART_COLS, GEMV_PART_COLS);
-    const int nblk = (int)std::min<int64_t>((n + GEMV_THREADS - 1) / GEMV_THREADS, GEMV_PART_BLOCKS);
+    const int nblk = gemv_t_blocks(n);
     if ((size_t)nblk * GEMV_PART_COLS > sizeof(scratch) / sizeof(double))
         return set_error(DMRG_E_INVALID_ARG, "partial sums of %d blocks exceed the fixed buffer", nblk);
     double *part = nullptr;
     DMRG_TRY(scratch_ptr(&part));
-    return gemv_t_launch(n, k, V, ldv, x, s, nblk, part, (hipStream_t)stream);
+    return gemv_t_launch(n, k, V, ldv, x, s, part, (hipStream_t)stream);
 }
