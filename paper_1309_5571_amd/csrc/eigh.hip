@@ -266,7 +266,7 @@ static_assert(HH_REG_DIM + HH_ROWS <= HH_VEC && HH_REG_DIM <= 192, "register red
 // nearer pole (a group of lanes per root: a two-pole rational model,
 // bracketed), the weights recomputed from the roots, and the rows of the
 // merged block of eigenvectors multiplied by the merge's eigenvector matrix
-// (two rows per wavefront, in place).
+// (FP64 MFMA, in place).  The merges of a level of the tree run side by side.
 constexpr int DC_MAX = 512;
 constexpr int DC_LEAF = 16;
 constexpr int DC_ITMAX = 100;  // root-finder steps per root (they end at the resolution, typically after 3-8)
@@ -307,11 +307,14 @@ __device__ __forceinline__ double rcpd(double x) {
     return fma(fma(-x, r, 1.0), r, r);
 }
 constexpr int DC_NLEAF = 32;    // most leaves: orders <= DC_MAX need at most 2^5 of at most DC_LEAF
-constexpr int DC_STAGE = 224;   // LDS staging of a row per wavefront (the pool's last 16 x 224)
 static_assert((DC_MAX + DC_NLEAF - 1) / DC_NLEAF <= DC_LEAF, "leaf count");
 // the pool (5 EIG_MAX_DIM doubles) holds the leaves, then the scratch of a merge
 static_assert(DC_NLEAF * DC_LEAF * (DC_LEAF + 1) + TRI_WAVES * (2 * DC_LEAF + 2) <= 5 * EIG_MAX_DIM, "leaf scratch");
-static_assert(13 * DC_MAX + 16 * DC_STAGE <= 5 * EIG_MAX_DIM, "merge scratch");
+static_assert(13 * DC_MAX <= 5 * EIG_MAX_DIM, "merge scratch");
+// a level's merges run on TRI_TPB >> t threads each: one wavefront at least, an
+// order of at most half as many threads, two panels of 16 roots a wavefront
+static_assert(DC_NLEAF / 2 <= TRI_WAVES && 2 * DC_MAX <= TRI_TPB && DC_MAX / 16 <= 2 * TRI_WAVES, "merge teams");
+typedef double v4d_eig __attribute__((ext_vector_type(4)));
 static_assert(QB * 64 * Q_REG <= 4 * EIG_MAX_DIM, "Q formation: factor vectors in the pool past the factors' t");
 
 // Implicit QL (as the large-order path) on a leaf of order m <= DC_LEAF, one
@@ -414,45 +417,159 @@ __device__ __forceinline__ int ql_leaf(int m, double *d, double *e, double *Zl, 
 // Scratch of one merge (LDS, carved from the pool): doubles of length DC_MAX
 struct DcScratch {
     double *zz, *ds, *rc, *rs, *delta, *zeta, *tau, *zhat, *invn, *lamn;
-    double *stage;  // [TRI_WAVES][DC_STAGE]: one row's weighted entries per wavefront
     int *perm, *defl, *rj, *ri, *nd, *tmp, *org;
 };
 
-// Merge of the solved halves [lo, mid) and [mid, hi) coupled by rho.  Zt:
+// The wavefronts that do one merge: 2^t merges of a level run side by side,
+// each on size = TRI_TPB >> t threads.  Every barrier is the workgroup's, so
+// all teams pass the same number of them.  A merge's time is a chain of
+// latencies (barriers, the root finder's iterations, one thread's deflation
+// scan) that more threads do not shorten; order 180, 15 merges one after the
+// other: 1.22 ms for the solve, four levels: 0.63 ms.
+struct DcTeam {
+    int size, waves, tid, wv;  // wv: the wavefront's index in the team
+};
+
+__device__ __forceinline__ double team_sum(double x, const DcTeam &tm, double *red) {
+    x = group_sum<64>(x);
+    const int wv = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) red[wv] = x;
+    __syncthreads();
+    double t = 0.0;
+    for (int i = 0; i < tm.waves; ++i) t += red[wv - tm.wv + i];
+    return t;
+}
+
+// Rank of v[i] among v[0..cnt) (ties by index), on G lanes that share i.
+__device__ __forceinline__ int dc_rank(const double *v, int cnt, int i, int g, int G) {
+    const double x = v[i];
+    int rk = 0;
+    for (int j = g; j < cnt; j += G) {
+        const double y = v[j];
+        rk += (y < x) || (y == x && j < i);
+    }
+    return (int)group_sum((double)rk, G);
+}
+
+// Rows [lo, hi) of the eigenvectors times the merge's eigenvector matrix
+// W(i, j) = zhat_i / (delta_i - lambda_j) / norm_j on FP64 MFMA, in place in the
+// columns of the k poles that are left.  A wavefront takes NP panels of 16 roots
+// and RT tiles of 16 rows at a time; its lanes form the entries of W (pole 4 s +
+// lane / 16, root lane % 16) where the product takes them, each once per group
+// of rows.  The team holds the products of a group of rows in registers until
+// all of it has read them.  (One wavefront per two rows, a reciprocal for every
+// entry of W and pair of rows, was bound by them: order 512, 23.1 ms for the
+// whole solve against 16.8.)
+template <int NP, int RT>
+__device__ __forceinline__ void dc_rows(int n, int lo, int hi, int k, int mmax, double *Zt, const DcScratch &S,
+                                        const DcTeam &tm) {
+    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
+    const size_t N = (size_t)n;
+    const double *dl = S.delta, *zh = S.zhat;
+    const int *col = S.tmp;
+    const int steps = (k + 3) >> 2;
+    double dj[NP], tj[NP];  // origin pole and offset of this lane's roots
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int j = min(16 * (tm.wv + p * tm.waves) + r16, max(k - 1, 0));
+        dj[p] = k > 0 ? dl[S.org[j]] : 0.0;
+        tj[p] = k > 0 ? S.tau[j] : 0.0;
+    }
+    for (int c0 = 0; c0 < mmax; c0 += 16 * RT) {
+        const int row0 = lo + c0, nt = min(RT, (hi - row0 + 15) >> 4);  // uniform
+        const bool work = 16 * tm.wv < k && nt > 0;
+        v4d_eig acc[NP][RT];
+        if (work) {
+            int off[RT];
+#pragma unroll
+            for (int q = 0; q < RT; ++q) {
+                off[q] = min(row0 + 16 * q + r16, hi - 1);
+#pragma unroll
+                for (int p = 0; p < NP; ++p) acc[p][q] = v4d_eig{0.0, 0.0, 0.0, 0.0};
+            }
+            auto load = [&](double (&x)[RT], int s) {
+                const double *c = Zt + (size_t)col[min(4 * s + g, k - 1)] * N;
+#pragma unroll
+                for (int q = 0; q < RT; ++q)
+                    if (q < nt) x[q] = c[off[q]];
+            };
+            auto step = [&](const double (&x)[RT], int s) {
+                const int i = min(4 * s + g, k - 1);
+                const double di = dl[i], zi = 4 * s + g < k ? zh[i] : 0.0;
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const double wij = zi * rcpd((di - dj[p]) - tj[p]);
+#pragma unroll
+                    for (int q = 0; q < RT; ++q)
+                        if (q < nt) acc[p][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(wij, x[q], acc[p][q], 0, 0, 0);
+                }
+            };
+            double x0[RT], x1[RT];
+            load(x0, 0);
+            for (int s = 0; s < steps; s += 2) {
+                load(x1, s + 1);
+                step(x0, s);
+                load(x0, s + 2);
+                if (s + 1 < steps) step(x1, s + 1);
+            }
+        }
+        __syncthreads();
+        if (work) {
+            // value v of lane (g, r16) is root 4 v + g of the panel, row r16 of the tile
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int j = 16 * (tm.wv + p * tm.waves) + 4 * v + g;
+                    if (j >= k) continue;
+                    const double inv = S.invn[j];
+                    double *c = Zt + (size_t)col[j] * N;
+#pragma unroll
+                    for (int q = 0; q < RT; ++q) {
+                        const int r = row0 + 16 * q + r16;
+                        if (r < hi) c[r] = acc[p][q][v] * inv;
+                    }
+                }
+        }
+    }
+}
+
+// Merge of the solved halves [lo, mid) and [mid, hi) coupled by rho, by one
+// team of the workgroup (mmax: the largest order of the level's merges).  Zt:
 // column-major n x n eigenvectors of T (rows and columns of the block only).
-__device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, double rho, double *sd, double *Zt, const DcScratch &S,
-                         double *red, int *ctl) {
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+// The columns keep their places: the eigenvalues of a merge are not sorted.
+__device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, int mmax, double rho, double *sd, double *Zt,
+                                         const DcScratch &S, const DcTeam &tm, double *red, int *ctl) {
+    const int tid = tm.tid;
     const size_t N = (size_t)n;
     const int m = hi - lo;
     // z: row mid - 1 of the left half's eigenvectors, row mid of the right half's
     double part = 0.0;
-    for (int c = tid; c < m; c += TRI_TPB) {
+    for (int c = tid; c < m; c += tm.size) {
         const int col = lo + c;
         double v = col < mid ? Zt[col * N + (mid - 1)] : Zt[col * N + mid];
         if (col >= mid && rho < 0.0) v = -v;
         S.zz[c] = v;
+        S.perm[c] = c;  // (poles that are not numbers have no rank)
         part += v * v;
     }
-    double unused;
-    const double nz2 = block_sum_lead(part, 0.0, red, &unused);
+    const double nz2 = team_sum(part, tm, red);
     const double rh = fabs(rho) * nz2;  // rho of the normalized z
-    if (!(rh > 0.0)) return;            // no coupling: the halves are already solved
+    const bool on = rh > 0.0;           // else no coupling: the halves are already solved
     const double inz = 1.0 / sqrt(nz2);
     // ascending order of the poles (ties by index)
-    for (int c = tid; c < m; c += TRI_TPB) {
-        const double x = sd[lo + c];
-        int rk = 0;
-        for (int j = 0; j < m; ++j) {
-            const double y = sd[lo + j];
-            rk += (y < x) || (y == x && j < c);
+    {
+        int G = 64;
+        while (G > 1 && G * m > tm.size) G >>= 1;
+        if (64 * tm.wv < G * m) {
+            const int c = min(tid / G, m - 1), g = tid & (G - 1);
+            const int rk = dc_rank(sd + lo, m, c, g, G);
+            if (tid / G < m && g == 0) {
+                S.perm[rk] = c;
+                S.ds[rk] = sd[lo + c];
+                S.zeta[rk] = S.zz[c] * inz;  // (zeta used as the sorted z during deflation)
+            }
         }
-        S.perm[rk] = c;
-    }
-    __syncthreads();
-    for (int t = tid; t < m; t += TRI_TPB) {
-        S.ds[t] = sd[lo + S.perm[t]];
-        S.zeta[t] = S.zz[S.perm[t]] * inz;  // (zeta used as the sorted z during deflation)
     }
     __syncthreads();
     // deflation (one thread, in pole order): a negligible weight leaves its pole;
@@ -462,7 +579,8 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, double 
     // <= tol is taken as |d_t - d_p| |z_t z_p| <= tol (z_p^2 + z_t^2) (no root: the
     // weights left are above tol / rh >= 8u, so the squares do not underflow).  A
     // pole joins the list of kept ones once the next one can no longer deflate it.
-    if (tid == 0) {
+    if (tid == 0 && !on) ctl[0] = ctl[1] = 0;
+    if (tid == 0 && on) {
         double *zs = S.zeta, *ds = S.ds;
         const double tol = 8.0 * 0x1p-53 * fmax(fmax(fabs(ds[0]), fabs(ds[m - 1])), rh);
         int nrot = 0, prev = -1, k = 0;
@@ -517,20 +635,26 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, double 
     }
     __syncthreads();
     const int k = ctl[0], nrot = ctl[1];
-    // the non-deflated poles in ascending order (a rotation may move one by a rounding)
-    for (int j = tid; j < k; j += TRI_TPB) {
-        const double x = S.ds[S.tmp[j]];
-        int rk = 0;
-        for (int i = 0; i < k; ++i) {
-            const double y = S.ds[S.tmp[i]];
-            rk += (y < x) || (y == x && i < j);
-        }
-        S.nd[rk] = S.tmp[j];
+    // the non-deflated poles in ascending order (a rotation may move one by a rounding);
+    // the poles by slot are in ds, those left are gathered in delta first
+    for (int j = tid; j < k; j += tm.size) {
+        S.nd[j] = S.tmp[j];
+        S.delta[j] = S.ds[S.tmp[j]];
     }
     __syncthreads();
-    for (int j = tid; j < k; j += TRI_TPB) {
-        S.delta[j] = S.ds[S.nd[j]];
-        S.zz[j] = S.zeta[S.nd[j]];  // zz: the weights of the non-deflated poles
+    int G = 64;
+    while (G > 1 && G * k > tm.size) G >>= 1;
+    if (64 * tm.wv < G * k) {
+        const int j = min(tid / G, k - 1), g = tid & (G - 1);
+        const int rk = dc_rank(S.delta, k, j, g, G);
+        if (tid / G < k && g == 0) S.nd[rk] = S.tmp[j];
+    }
+    __syncthreads();
+    for (int j = tid; j < k; j += tm.size) {
+        const int t = S.nd[j];
+        S.delta[j] = S.ds[t];
+        S.zz[j] = S.zeta[t];           // zz: the weights of the non-deflated poles
+        S.tmp[j] = lo + S.perm[t];     // tmp: their columns
     }
     __syncthreads();
     // roots of the secular equation: root j lies between delta[j] and delta[j+1]
@@ -543,10 +667,8 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, double 
     // holds the same values and takes the same steps; a wavefront iterates
     // until all of its roots have stopped, finished roots keeping their value.
     const double *dl = S.delta, *zw = S.zz;
-    int G = 64;
-    while (G > 1 && G * k > TRI_TPB) G >>= 1;
-    if (64 * wv < G * k) {  // wavefronts past the last root's group have nothing to do
-        const int g = lane & (G - 1), jr = tid / G, j = min(jr, k - 1);
+    if (64 * tm.wv < G * k) {  // wavefronts past the last root's group have nothing to do
+        const int g = tid & (G - 1), jr = tid / G, j = min(jr, k - 1);
         double part = 0.0;
         for (int i = g; i < k; i += G) part += zw[i] * zw[i];
         const double zsum = group_sum(part, G);
@@ -630,8 +752,8 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, double 
     // weights recomputed from the roots (their signs kept), then the norms of
     // the eigenvectors zhat_i / (delta_i - lambda_j); G lanes per weight (per
     // norm) split the product (the sum) over the poles, as for the roots
-    if (64 * wv < G * k) {
-        const int g = lane & (G - 1), ir = tid / G, i = min(ir, k - 1);
+    if (64 * tm.wv < G * k) {
+        const int g = tid & (G - 1), ir = tid / G, i = min(ir, k - 1);
         double prod = 1.0;
         for (int j = g; j < k; j += G)
             if (j != i) prod *= ((dl[S.org[j]] - dl[i]) + S.tau[j]) * rcpd(dl[j] - dl[i]);
@@ -639,8 +761,8 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, double 
         if (ir < k && g == 0) S.zhat[i] = copysign(sqrt(fmax(prod, 0.0)), zw[i]);
     }
     __syncthreads();
-    if (64 * wv < G * k) {
-        const int g = lane & (G - 1), jr = tid / G, j = min(jr, k - 1);
+    if (64 * tm.wv < G * k) {
+        const int g = tid & (G - 1), jr = tid / G, j = min(jr, k - 1);
         const double dj = dl[S.org[j]], tj = S.tau[j];
         double q = 0.0;
         for (int i = g; i < k; i += G) {
@@ -653,83 +775,46 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, double 
             S.lamn[j] = dj + tj;
         }
     }
-    __syncthreads();
-    // the deflation rotations on the columns of the block (in pole order)
-    for (int q = 0; q < nrot; ++q) {
-        const size_t cj = (size_t)(lo + S.perm[S.rj[q]]) * N, ci = (size_t)(lo + S.perm[S.ri[q]]) * N;
-        const double c = S.rc[q], sn = S.rs[q];
-        for (int r = lo + tid; r < hi; r += TRI_TPB) {
-            const double yj = Zt[cj + r], yi = Zt[ci + r];
-            Zt[cj + r] = c * yj + sn * yi;
-            Zt[ci + r] = c * yi - sn * yj;
-        }
-        __syncthreads();
-    }
-    // rows of the block times the merge's eigenvectors: slot t of the block takes
-    // pole t (in pole order); a deflated slot keeps its column, the slot of the
-    // non-deflated pole nd[j] gets root j's eigenvector.  One wavefront per two
-    // rows: their weighted entries y_i zhat_i are staged in LDS and read by every
-    // lane, each lane accumulating the outputs of its roots j = lane + 64 q, one
-    // reciprocal serving both rows.
-    constexpr int NQ = DC_MAX / 64;
-    constexpr int CH = DC_STAGE / 2;  // entries of each row per staging round
-    double djr[NQ], tjr[NQ];  // origin pole and offset of this lane's roots
+    // the deflation rotations on the columns of the block (in pole order), each
+    // thread on its own rows.  A column is the later one of at most one rotation,
+    // and if it is the earlier one of another, then of the next: its value is
+    // carried, and every load takes a column that no rotation has changed.
+    constexpr int ROT = 4;  // rotations per batch of loads
+    for (int r = lo + tid; r < hi; r += tm.size) {
+        double carry = 0.0;
+        int have = -1;  // slot of the carried column
+        for (int q0 = 0; q0 < nrot; q0 += ROT) {
+            double xj[ROT], xi[ROT];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const int j = lane + 64 * q;
-        djr[q] = j < k ? dl[S.org[j]] : 0.0;
-        tjr[q] = j < k ? S.tau[j] : -1.0;  // (past k: a finite, unused difference)
-    }
-    double *st = S.stage + wv * DC_STAGE;  // [CH][2]
-    for (int r = lo + 2 * wv; r < hi; r += 2 * TRI_WAVES) {
-        const bool two = r + 1 < hi;  // uniform
-        double yd[2][NQ], acc[2][NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int t = lane + 64 * q;
-            acc[0][q] = acc[1][q] = 0.0;
-            yd[0][q] = (64 * q < m && t < m) ? Zt[(size_t)(lo + S.perm[t]) * N + r] : 0.0;
-            yd[1][q] = (two && 64 * q < m && t < m) ? Zt[(size_t)(lo + S.perm[t]) * N + r + 1] : 0.0;
-        }
-        for (int c0 = 0; c0 < k; c0 += CH) {
-            const int cnt = min(CH, k - c0);
-            for (int e = lane; e < cnt; e += 64) {
-                const int i = c0 + e;
-                const double *src = Zt + (size_t)(lo + S.perm[S.nd[i]]) * N;
-                const double zh = S.zhat[i];
-                st[2 * e] = src[r] * zh;
-                st[2 * e + 1] = two ? src[r + 1] * zh : 0.0;
+            for (int u = 0; u < ROT; ++u) {
+                const int q = min(q0 + u, nrot - 1);
+                xj[u] = Zt[(size_t)(lo + S.perm[S.rj[q]]) * N + r];
+                xi[u] = Zt[(size_t)(lo + S.perm[S.ri[q]]) * N + r];
             }
-            wave_sync_lds();
-            for (int e = 0; e < cnt; ++e) {
-                const double ya = st[2 * e], yb = st[2 * e + 1], di = dl[c0 + e];
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    if (64 * q >= k) break;  // uniform: the root slots past k are not computed
-                    const double rc = rcpd((di - djr[q]) - tjr[q]);
-                    acc[0][q] += ya * rc;
-                    acc[1][q] += yb * rc;
-                }
-            }
-            wave_sync_lds();  // the next chunk rewrites the staging slice
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (h == 1 && !two) break;
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int i = lane + 64 * q;
-                if (64 * q < m) {
-                    if (i < k) Zt[(size_t)(lo + S.nd[i]) * N + r + h] = acc[h][q] * S.invn[i];
-                    if (i < m && S.defl[i]) Zt[(size_t)(lo + i) * N + r + h] = yd[h][q];
-                }
+            for (int u = 0; u < ROT; ++u) {
+                const int q = q0 + u;
+                if (q >= nrot) break;
+                const int sj = S.rj[q], si = S.ri[q];
+                const double c = S.rc[q], sn = S.rs[q];
+                const double yj = sj == have ? carry : xj[u], yi = xi[u];
+                Zt[(size_t)(lo + S.perm[sj]) * N + r] = c * yj + sn * yi;
+                carry = c * yi - sn * yj;
+                have = si;
+                if (q + 1 == nrot || S.rj[q + 1] != si) Zt[(size_t)(lo + S.perm[si]) * N + r] = carry;
             }
         }
     }
     __syncthreads();
-    for (int t = tid; t < m; t += TRI_TPB)
-        if (S.defl[t]) sd[lo + t] = S.ds[t];
-    for (int j = tid; j < k; j += TRI_TPB) sd[lo + S.nd[j]] = S.lamn[j];
+    if (n <= 256)
+        dc_rows<1, 6>(n, lo, hi, k, mmax, Zt, S, tm);
+    else
+        dc_rows<2, 4>(n, lo, hi, k, mmax, Zt, S, tm);
+    if (on) {
+        for (int t = tid; t < m; t += tm.size)
+            if (S.defl[t]) sd[lo + S.perm[t]] = S.ds[t];
+        for (int j = tid; j < k; j += tm.size) sd[S.tmp[j]] = S.lamn[j];
+    }
     __syncthreads();
 }
 
@@ -786,31 +871,35 @@ __device__ __forceinline__ void dc_solve(int n, double *sd, double *se, double *
     __syncthreads();
     // merges, deepest level first
     DcScratch S;
-    S.zz = pool;
-    S.ds = pool + DC_MAX;
-    S.rc = pool + 2 * DC_MAX;
-    S.rs = pool + 3 * DC_MAX;
-    S.delta = pool + 4 * DC_MAX;
-    S.zeta = pool + 5 * DC_MAX;
-    S.tau = pool + 6 * DC_MAX;
-    S.zhat = pool + 7 * DC_MAX;
-    S.invn = pool + 8 * DC_MAX;
-    S.lamn = pool + 9 * DC_MAX;
-    int *ip = (int *)(pool + 10 * DC_MAX);
-    S.perm = ip;
-    S.defl = ip + DC_MAX;
-    S.rj = ip + 2 * DC_MAX;
-    S.ri = ip + 3 * DC_MAX;
-    S.nd = ip + 4 * DC_MAX;
-    S.tmp = ip + 5 * DC_MAX;
-    S.org = ipool;
-    S.stage = pool + 13 * DC_MAX;
-    for (int t = T - 1; t >= 0; --t)
-        for (int i = 0; i < (1 << t); ++i) {
-            const int lo = bnd(t, i), mid = bnd(t + 1, 2 * i + 1), hi = bnd(t, i + 1);
-            if (lo < mid && mid < hi) dc_merge(n, lo, mid, hi, se[mid - 1], sd, Zt, S, red, ctl);
-            if (tid == 0) ++ctl[3];
-        }
+    for (int t = T - 1; t >= 0; --t) {
+        DcTeam tm;
+        tm.size = TRI_TPB >> t;
+        tm.waves = TRI_WAVES >> t;
+        tm.tid = tid & (tm.size - 1);
+        tm.wv = wv & (tm.waves - 1);
+        const int i = tid / tm.size;
+        const int lo = bnd(t, i), mid = bnd(t + 1, 2 * i + 1), hi = bnd(t, i + 1);
+        S.zz = pool + lo;
+        S.ds = S.zz + DC_MAX;
+        S.rc = S.ds + DC_MAX;
+        S.rs = S.rc + DC_MAX;
+        S.delta = S.rs + DC_MAX;
+        S.zeta = S.delta + DC_MAX;
+        S.tau = S.zeta + DC_MAX;
+        S.zhat = S.tau + DC_MAX;
+        S.invn = S.zhat + DC_MAX;
+        S.lamn = S.invn + DC_MAX;
+        S.perm = (int *)(pool + 10 * DC_MAX) + lo;
+        S.defl = S.perm + DC_MAX;
+        S.rj = S.defl + DC_MAX;
+        S.ri = S.rj + DC_MAX;
+        S.nd = S.ri + DC_MAX;
+        S.tmp = S.nd + DC_MAX;
+        S.org = ipool + lo;
+        int *tctl = ipool + DC_MAX + 2 * i;
+        dc_merge(n, lo, mid, hi, (n + (1 << t) - 1) >> t, se[mid - 1], sd, Zt, S, tm, red, tctl);
+    }
+    if (tid == 0) ctl[3] += nleaf - 1;  // merges
     __syncthreads();
 }
 
