@@ -11,14 +11,14 @@
 // whole sub-blocks.  A sweep is d - 1 rounds (every pair once); the method
 // stops after a sweep with no rotation.
 //
-// 8 < d <= 2048: Householder reduction to tridiagonal form T = Q^T A Q, the
-// matrix Q formed explicitly, then T's eigenpairs.  The reduction and the
-// formation of Q are whole-workgroup passes over the block (in global memory,
-// where it stays cache-resident).  Orders up to 512: Cuppen's divide and
-// conquer on T (leaves of at most 16 by implicit QL, one wavefront each;
-// merges by deflation, the secular equation on a group of lanes per root and
-// Gu and Eisenstat's recomputed weights), then the eigenvectors of the block
-// as Q times those of T.  Larger orders: the implicit QL iteration with
+// 8 < d <= 2048: Householder reduction to tridiagonal form T = Q^T A Q (in
+// registers up to order 180, above in global memory, where the block stays
+// cache-resident), then T's eigenpairs.  Orders up to 512: Cuppen's divide and
+// conquer on T (leaves of at most 16 by implicit QL, one wavefront each; merges
+// by deflation, the secular equation on a group of lanes per root and Gu and
+// Eisenstat's recomputed weights), then the reflectors of Q applied to its
+// eigenvectors, 16 columns a workgroup.  Larger orders: Q formed, and the
+// implicit QL iteration with
 // Wilkinson's shift on T (the tql2 procedure of Bowdler, Martin, Reinsch and
 // Wilkinson), whose plane rotations are applied to the columns of Q: the QL
 // recurrence is sequential and runs on one lane, writing each sweep's
@@ -33,8 +33,7 @@
 namespace dmrg {
 
 constexpr int EIG_TPB = 256;        // selection kernel
-constexpr int EIG_TPB_SMALL = 512;  // Jacobi, blocks in LDS (a round has ~d^2/2 independent items)
-constexpr int EIG_LDS_DIM = 8;  // largest order of the Jacobi kernel (larger ones are faster on the tridiagonal path)
+constexpr int EIG_LDS_DIM = 8;  // largest order of the Jacobi method (larger ones are faster on the tridiagonal path)
 constexpr int EIG_MAX_DIM = 2048;
 constexpr int EIG_MAX_SWEEPS = 40;
 constexpr int TRI_TPB = 1024;  // tridiagonal path
@@ -53,38 +52,23 @@ __device__ __forceinline__ void circle_pair(int r, int k, int m, int &p, int &q)
     }
 }
 
-__global__ __launch_bounds__(EIG_TPB_SMALL) void k_eigh_jacobi(int nblk, const int64_t *__restrict__ off,
-                                                               const int32_t *__restrict__ dim,
-                                                               const int64_t *__restrict__ woff, double *__restrict__ a,
-                                                               double *__restrict__ w, double *__restrict__ u,
-                                                               int32_t *__restrict__ info) {
+// One block of order d <= EIG_LDS_DIM, by the whole workgroup; lds: JAC_LDS doubles.
+constexpr int JAC_LDS = 3 * EIG_LDS_DIM * EIG_LDS_DIM + 5 * EIG_LDS_DIM;
+__device__ __forceinline__ void eigh_jacobi(int d, const double *in, double *wb, double *out, int32_t *info,
+                                            double *lds) {
     constexpr int NP = EIG_LDS_DIM / 2;  // pairs per round
-    constexpr int NT = EIG_TPB_SMALL;
-    __shared__ double A[EIG_LDS_DIM * (EIG_LDS_DIM + 1)];
-    __shared__ double V[EIG_LDS_DIM * EIG_LDS_DIM];
-    __shared__ double rc[NP], rs[NP];
-    __shared__ int rp[NP], rq[NP], rf[NP];
-    __shared__ double part[NT];
-    __shared__ double diag[EIG_LDS_DIM];
-    const int b = blockIdx.x;
-    if (b >= nblk) return;
-    const int d = dim[b];
+    constexpr int NT = TRI_TPB;
+    constexpr int NE = EIG_LDS_DIM * EIG_LDS_DIM;
+    double *V = lds, *part = V + NE, *A = part + NE, *diag = A + NE + EIG_LDS_DIM;
+    double *rc = diag + EIG_LDS_DIM, *rs = rc + NP;
+    int *rp = (int *)(rs + NP), *rq = rp + NP, *rf = rq + NP;
     const int tid = threadIdx.x;
-    if (d < 1 || d > EIG_MAX_DIM) {
-        if (tid == 0 && info) info[b] = -1;  // unsupported order
-        return;
-    }
-    if (d > EIG_LDS_DIM) return;  // the tridiagonal kernel's block
-    const double *in = a + off[b];
-    double *out = u + off[b];
     const int lda = d + 1;
-    double fro = 0.0;
-    for (int e = tid; e < d * d; e += NT) fro += in[e] * in[e];
-    part[tid] = fro;
+    if (tid < NE) part[tid] = tid < d * d ? in[tid] * in[tid] : 0.0;
     __syncthreads();
     if (tid == 0) {
         double s = 0.0;
-        for (int i = 0; i < NT; ++i) s += part[i];
+        for (int i = 0; i < NE; ++i) s += part[i];
         part[0] = sqrt(s);
     }
     __syncthreads();
@@ -177,7 +161,6 @@ __global__ __launch_bounds__(EIG_TPB_SMALL) void k_eigh_jacobi(int nblk, const i
     // first entry of largest magnitude positive
     for (int i = tid; i < d; i += NT) diag[i] = A[i * lda + i];
     __syncthreads();
-    double *wb = w + woff[b];
     for (int i = tid; i < d; i += NT) {
         const double wi = diag[i];
         int rank = 0;
@@ -198,7 +181,7 @@ __global__ __launch_bounds__(EIG_TPB_SMALL) void k_eigh_jacobi(int nblk, const i
         wb[rank] = wi;
         for (int r = 0; r < d; ++r) out[r * d + rank] = sg * V[r * d + i];
     }
-    if (tid == 0 && info) info[b] = done ? sweep : -2;
+    if (tid == 0 && info) *info = done ? sweep : -2;
 }
 
 // Sum over the workgroup of one value per thread, and the value `lead` of
@@ -246,11 +229,11 @@ constexpr int TRI_UB = 16;  // rows of a column read per batch of loads (Househo
 constexpr int QL_B = 8;     // rotations applied per batch of loads (QL; the next batch is fetched ahead)
 constexpr int Q_REG = 8;    // column entries per lane kept in registers (Q formation, L <= 512)
 constexpr int QB = 16;      // factors per block of the Q formation (their vectors: QB x 512 doubles of LDS)
-constexpr int HH_ROWS = 36;     // rows of the block per thread (Householder reduction in registers, orders 129..)
-constexpr int HH_REG_DIM = 180; // largest order reduced in registers (five groups of HH_ROWS rows)
-constexpr int HH_VEC = 256;     // LDS vectors of that reduction: past the order up to the last group's end
-static_assert(TRI_WAVES == 16 && 5 * HH_ROWS >= HH_REG_DIM && 8 * 16 >= 128 && 16 * 4 >= 64, "register rows");
-static_assert(HH_REG_DIM + HH_ROWS <= HH_VEC && HH_REG_DIM <= 192, "register reduction vectors");
+constexpr int HH_WAVES = TRI_WAVES - 1;       // wavefronts with rows of the block (Householder reduction in registers)
+constexpr int HH_REG_DIM = HH_WAVES * 4 * 3;  // largest order reduced there: 12 rows of three columns a thread
+constexpr int HH_VEC = 64 * 3;                // LDS vectors of that reduction
+static_assert(HH_REG_DIM <= HH_VEC, "vectors as long as the order");
+static_assert(JAC_LDS <= TRI_TPB, "the Jacobi method in the partial products' place");
 
 // ------------------------------------------------------------------ divide and conquer
 // The symmetric tridiagonal eigenproblem of orders up to DC_MAX by Cuppen's
@@ -903,161 +886,189 @@ __device__ __forceinline__ void dc_solve(int n, double *sd, double *se, double *
     __syncthreads();
 }
 
-// Householder reduction with the block in registers, R rows per thread: the
-// wavefront wv keeps the entries (j, c) of the rows j0 <= j < j0 + R of its
-// group g = wv / CB and of the column c = 64 (wv % CB) + lane, so that only
-// vectors pass through LDS (zero past the order, so that rows past it add
-// nothing).  Step k: column k (left in scol by the previous step's pass, with
-// step k - 1's update still to apply: (v', w') pairs in cur) gives the
-// diagonal and the reflector (v into nxt, also stored in row k beyond k + 1
-// for the Q formation); then rows and columns k + 1.. take step k - 1's
-// update and are multiplied by v in one pass, which also leaves column k + 1
-// in scol; the groups' partial products meet in LDS (spart) as p = t A v, and
-// w = p - K v goes next to v in nxt, the next step's pending update.  Each
-// entry is updated by its own thread (A(i, j) and A(j, i) may differ by
-// roundings; every step reads the block by columns).
-template <int R>
+// Householder reduction with the block in registers, R = 4 NQ rows by NQ
+// columns a thread: the wavefront wv keeps the rows R wv .. of the columns lane
+// + 64 q, so that only vectors pass through LDS (zero past the order, so that
+// rows and columns past it add nothing).  The last wavefront keeps no rows but
+// the vectors, and forms each step's scalars between two barriers.  Step k: row
+// k (left in srow by the previous step's pass, with step k - 1's update (v', w')
+// still to apply) gives the diagonal and the reflector v (into LDS, and stored
+// in row k beyond k + 1 for the back-transformation); then rows and columns k +
+// 1.. take step k - 1's update and are multiplied by v in one pass, which also
+// leaves row k + 1 in srow; the wavefronts' partial products meet in LDS (spart)
+// as p = t A v, and w = p - K v goes next to v, the next step's pending update.
+// Each entry is updated by its own thread (A(i, j) and A(j, i) may differ by
+// roundings).
+// What bounds it: the LDS reads that every lane makes of a row's entries (one
+// serves NQ columns; with one column a thread they took most of a step) and the
+// chain of the scalars, which one wavefront does in the shortest time: with all
+// 16 forming them, or joining reductions for them, 4 wavefronts a SIMD issue the
+// same instructions.  Order 180: 612 -> 299 us (1.7 us a step), 32: 54 -> 25.
+template <int NQ>
+__device__ __forceinline__ double hh_pick(const double (&x)[NQ], int q) {  // x[q], q uniform
+    const double x1 = x[NQ > 1 ? 1 : 0], x2 = x[NQ > 2 ? 2 : 0];
+    double y = x[0];
+    if (NQ > 1) y = q >= 1 ? x1 : y;
+    if (NQ > 2) y = q >= 2 ? x2 : y;
+    return y;
+}
+
+template <int NQ>
 __device__ __forceinline__ void hh_reduce(int d, const double *Z, double *A, double *wb, double2 *P0, double2 *P1,
-                                          double *scol, double *spart, double *red, double *red2) {
+                                          double *srow, double *spart) {
+    constexpr int R = 4 * NQ, LD = 64 * NQ;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // (so that the rows, and their tests, are scalar)
     const size_t D = (size_t)d;
-    const int CB = (d + 63) >> 6, G = (d + R - 1) / R;
-    const int g = wv / CB, cb = wv % CB, c = cb * 64 + lane;
-    const bool act = g < G;  // (uniform: the wavefronts past the groups only join the reductions)
-    const int j0 = g * R;
-    const int jv = ((tid >> 6) / CB) * R;  // j0 in a vector register: LDS rows at immediate offsets from it
-    double a[R];
-#pragma unroll
-    for (int q = 0; q < R; ++q) a[q] = (act && j0 + q < d && c < d) ? Z[(size_t)(j0 + q) * D + c] : 0.0;
     for (int j = tid; j < HH_VEC; j += TRI_TPB) {
         P0[j] = make_double2(0.0, 0.0);  // no update pending before step 0
         P1[j] = make_double2(0.0, 0.0);
-        scol[j] = j < d ? Z[(size_t)j * D] : 0.0;  // column 0
+        srow[j] = j < d ? Z[j] : 0.0;  // row 0
     }
     __syncthreads();
     double2 *cur = P0, *nxt = P1;
-    for (int k = 0; k + 2 < d; ++k) {
-        // column k after step k - 1's update: the diagonal, and x into nxt
-        double part = 0.0, lead = 0.0;
-        bool own = false;
-        {
-            const double2 pk = cur[k];
-            for (int j = k + tid; j < d; j += TRI_TPB) {
-                const double2 pj = cur[j];
-                const double x = fma(-pj.x, pk.y, fma(-pj.y, pk.x, scol[j]));
-                if (j == k) {
-                    wb[k] = x;
-                } else {
-                    nxt[j].x = x;
-                    if (j == k + 1) {
-                        own = true;
-                        lead = x;
-                    } else {
-                        part += x * x;
-                    }
-                }
-            }
-        }
-        double alpha;  // x(0), handed over by its thread (nxt[k + 1] is rewritten below)
-        const double sigma = block_sum1(part, own, lead, red2, &alpha);
-        double t = 0.0;
-        if (sigma == 0.0) {  // the column is already reduced: t = 0
-            for (int j = k + 1 + tid; j < d; j += TRI_TPB) {
-                nxt[j].x = j == k + 1 ? 1.0 : 0.0;
-                if (j > k + 1) A[k * D + j] = 0.0;
-            }
-            if (tid == 0) {
-                A[(k + 1) * D + k] = alpha;
-                A[(k + 2) * D + k] = 0.0;
-            }
-        } else {
-            const double beta = -copysign(sqrt(alpha * alpha + sigma), alpha);
-            t = (beta - alpha) / beta;
-            const double scale = 1.0 / (alpha - beta);
-            for (int j = k + 1 + tid; j < d; j += TRI_TPB) {
-                const double vj = j == k + 1 ? 1.0 : nxt[j].x * scale;
-                nxt[j].x = vj;
-                if (j > k + 1) A[k * D + j] = vj;
-            }
-            if (tid == 0) {
-                A[(k + 1) * D + k] = beta;
-                A[(k + 2) * D + k] = t;
-            }
-        }
-        __syncthreads();
-        // rows and columns k + 1..: step k - 1's update, and the product with v;
-        // column k + 1 into scol
-        double acc = 0.0;
-        if (act && cb * 64 + 63 > k) {  // (uniform: a column block left of k + 1 is finished)
-            const double2 pc = cur[c];
-            const double2 *pr = cur + jv, *pn = nxt + jv;
-            double *sc = scol + jv;
-            const bool next = c == k + 1;
-            // the rows past k form a suffix; each row's LDS reads are issued one
-            // row ahead, so that their latency overlaps the previous row's work
-            const int qs = max(0, min(R, k + 1 - j0));
-            double2 nr = qs < R ? pr[qs] : make_double2(0.0, 0.0);
-            double nv = qs < R ? pn[qs].x : 0.0;
+    if (wv < HH_WAVES) {
+        const int j0 = wv * R;
+        double a[R][NQ];
 #pragma unroll
-            for (int q = 0; q < R; ++q) {
-                if (j0 + q > k) {  // (uniform)
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int c = lane + 64 * q;
+                a[r][q] = (j0 + r < d && c < d) ? Z[(size_t)(j0 + r) * D + c] : 0.0;
+            }
+        for (int k = 0; k + 2 < d; ++k) {
+            __syncthreads();  // v of step k and w of step k - 1 are in LDS
+            // rows and columns k + 1..: step k - 1's update, and the product with v;
+            // row k + 1 into srow
+            if (j0 + R > k + 1 && j0 < d) {  // (uniform: rows that are not finished)
+                double2 pc[NQ];
+                double acc[NQ];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    pc[q] = cur[lane + 64 * q];
+                    acc[q] = 0.0;
+                }
+                const double2 *pr = cur + j0, *pn = nxt + j0;
+                // each row's LDS reads are issued one row ahead, so that their
+                // latency overlaps the previous row's work; v is zero up to row k
+                double2 nr = pr[0];
+                double nv = pn[0].x;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
                     const double2 pj = nr;
-                    const double vq = nv;
-                    if (q + 1 < R) {
-                        nr = pr[q + 1];
-                        nv = pn[q + 1].x;
+                    const double vr = nv;
+                    if (r + 1 < R) {
+                        nr = pr[r + 1];
+                        nv = pn[r + 1].x;
                     }
-                    const double x = fma(-pj.x, pc.y, fma(-pj.y, pc.x, a[q]));
-                    a[q] = x;
-                    acc = fma(x, vq, acc);
-                    if (next) sc[q] = x;
-                }
-            }
-        }
-        spart[tid] = acc;
-        __syncthreads();
-        // p = t A v (column tid), K = t p.v / 2, w = p - K v
-        const bool mine = tid > k && tid < d;
-        double pc = 0.0, pv = 0.0, vt = 0.0;
-        if (mine) {
-            double sum = 0.0;
-            for (int gg = 0; gg < G; ++gg) sum += spart[(gg * CB + (tid >> 6)) * 64 + (tid & 63)];
-            pc = t * sum;
-            vt = nxt[tid].x;
-            pv = pc * vt;
-        }
-        double unused;
-        const double K = 0.5 * t * block_sum1(pv, false, 0.0, red, &unused);
-        if (mine) nxt[tid].y = pc - K * vt;
-        double2 *tmp = cur;  // (v, w) of this step is the next step's pending update
-        cur = nxt;
-        nxt = tmp;
-        __syncthreads();
-    }
-    // the trailing 2 x 2 after the last step's update: column d - 2 from scol,
-    // the entry (d - 1, d - 1) from its thread
-    const int k = d - 2;
-    if (tid < 2) {
-        const int j = k + tid;
-        const double2 pk = cur[k], pj = cur[j];
-        const double x = fma(-pj.x, pk.y, fma(-pj.y, pk.x, scol[j]));
-        if (tid == 0)
-            wb[k] = x;
-        else
-            A[(k + 1) * D + k] = x;
-    }
-    if (act && c == d - 1) {
-        double ad = 0.0;
-        bool has = false;
 #pragma unroll
-        for (int q = 0; q < R; ++q)
-            if (j0 + q == d - 1) {
-                ad = a[q];
-                has = true;
+                    for (int q = 0; q < NQ; ++q) {
+                        const double x = fma(-pj.x, pc[q].y, fma(-pj.y, pc[q].x, a[r][q]));
+                        a[r][q] = x;
+                        acc[q] = fma(x, vr, acc[q]);
+                    }
+                    if (j0 + r == k + 1) {  // (uniform)
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q) srow[lane + 64 * q] = a[r][q];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) spart[wv * LD + 64 * q + lane] = acc[q];
             }
+            __syncthreads();
+            double2 *tmp = cur;
+            cur = nxt;
+            nxt = tmp;
+        }
+        __syncthreads();
+        // the entry (d - 1, d - 1) after the last step's update
         const double2 pd = cur[d - 1];
-        if (has) wb[d - 1] = fma(-pd.x, pd.y, fma(-pd.y, pd.x, ad));
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+                if (j0 + r == d - 1 && lane + 64 * q == d - 1) wb[d - 1] = fma(-pd.x, pd.y, fma(-pd.y, pd.x, a[r][q]));
+    } else {
+        const int G = (d + R - 1) / R;  // wavefronts that have rows
+        double v[NQ], w[NQ], t = 0.0;   // the last step's reflector, the update pending before it
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) v[q] = w[q] = 0.0;
+        // p = t A v, K = t p.v / 2, w = p - K v: step k's update, pending in buf
+        auto update = [&](int k, double2 *buf) {
+            double p[NQ], pv = 0.0;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) p[q] = 0.0;
+#pragma unroll 4
+            for (int g = (k + 1) / R; g < G; ++g)  // (the rows past k)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) p[q] += spart[g * LD + 64 * q + lane];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                p[q] = lane + 64 * q > k ? t * p[q] : 0.0;
+                pv += p[q] * v[q];
+            }
+            const double K = 0.5 * t * group_sum<64>(pv);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                w[q] = p[q] - K * v[q];
+                buf[lane + 64 * q].y = w[q];
+            }
+        };
+        for (int k = 0; k + 2 < d; ++k) {
+            if (k > 0) update(k - 1, cur);
+            // row k after step k - 1's update: the diagonal and x
+            const double vk = readlane_f64(hh_pick<NQ>(v, k >> 6), k & 63);
+            const double wk = readlane_f64(hh_pick<NQ>(w, k >> 6), k & 63);
+            double x[NQ], part = 0.0;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int j = lane + 64 * q;
+                x[q] = fma(-v[q], wk, fma(-w[q], vk, srow[j]));
+                part += j > k + 1 ? x[q] * x[q] : 0.0;  // (zero past the order)
+            }
+            const double sigma = group_sum<64>(part);
+            const double alpha = readlane_f64(hh_pick<NQ>(x, (k + 1) >> 6), (k + 1) & 63);
+            double beta = alpha, scale = 0.0;
+            t = 0.0;  // sigma = 0: the row is already reduced
+            if (sigma != 0.0) {
+                beta = -copysign(sqrt(alpha * alpha + sigma), alpha);
+                t = (beta - alpha) / beta;
+                scale = 1.0 / (alpha - beta);
+            }
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int j = lane + 64 * q;
+                v[q] = j <= k ? 0.0 : (j == k + 1 ? 1.0 : (sigma != 0.0 ? x[q] * scale : 0.0));
+                nxt[j].x = v[q];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int j = lane + 64 * q;
+                if (j > k + 1 && j < d) A[k * D + j] = v[q];
+                if (j == k) wb[k] = x[q];
+                if (j == k + 1) A[j * D + k] = beta;
+                if (j == k + 2) A[j * D + k] = t;
+            }
+            __syncthreads();
+            double2 *tmp = cur;
+            cur = nxt;
+            nxt = tmp;
+        }
+        update(d - 3, cur);
+        // the diagonal entry and the coupling of row d - 2 after the last step's update
+        const int k = d - 2;
+        const double vk = readlane_f64(hh_pick<NQ>(v, k >> 6), k & 63);
+        const double wk = readlane_f64(hh_pick<NQ>(w, k >> 6), k & 63);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int j = lane + 64 * q;
+            const double x = fma(-v[q], wk, fma(-w[q], vk, srow[j]));
+            if (j == k) wb[k] = x;
+            if (j == k + 1) A[j * D + k] = x;
+        }
+        __syncthreads();
     }
 }
 
@@ -1070,31 +1081,37 @@ __device__ __forceinline__ void hh_reduce(int d, const double *Z, double *A, dou
 __global__ __launch_bounds__(TRI_TPB) void k_eigh_hh(int nblk, const int64_t *__restrict__ off,
                                                      const int32_t *__restrict__ dim, const int64_t *__restrict__ woff,
                                                      const double *__restrict__ a, double *__restrict__ w,
-                                                     double *__restrict__ u) {
+                                                     double *__restrict__ u, int32_t *__restrict__ info) {
     __shared__ double2 P0[HH_VEC], P1[HH_VEC];  // (v, w) of two steps
-    __shared__ double scol[HH_VEC];
-    __shared__ double spart[TRI_TPB];
-    __shared__ double red[TRI_WAVES + 1], red2[TRI_WAVES + 1];
+    __shared__ double srow[HH_VEC];
+    __shared__ double spart[TRI_WAVES * HH_VEC];
     const int b = blockIdx.x;
     if (b >= nblk) return;
     const int d = dim[b];
-    if (d <= EIG_LDS_DIM || d > HH_REG_DIM) return;
+    if (d < 1 || d > EIG_MAX_DIM) {
+        if (threadIdx.x == 0 && info) info[b] = -1;  // unsupported order
+        return;
+    }
+    if (d > HH_REG_DIM) return;  // reduced by k_eigh_tri
     const double *Z = a + off[b];
     double *A = u + off[b], *wb = w + woff[b];
-    // rows per thread: 4, 16 or 36 for one, two or three column blocks of 64
-    if (d <= 64)
-        hh_reduce<4>(d, Z, A, wb, P0, P1, scol, spart, red, red2);
-    else if (d <= 128)
-        hh_reduce<16>(d, Z, A, wb, P0, P1, scol, spart, red, red2);
+    if (d <= EIG_LDS_DIM) {
+        eigh_jacobi(d, Z, wb, A, info ? info + b : nullptr, spart);
+        return;
+    }
+    if (d <= HH_WAVES * 4)
+        hh_reduce<1>(d, Z, A, wb, P0, P1, srow, spart);
+    else if (d <= HH_WAVES * 8)
+        hh_reduce<2>(d, Z, A, wb, P0, P1, srow, spart);
     else
-        hh_reduce<HH_ROWS>(d, Z, A, wb, P0, P1, scol, spart, red, red2);
+        hh_reduce<3>(d, Z, A, wb, P0, P1, srow, spart);
 }
 
 // Tridiagonal path of the orders EIG_LDS_DIM + 1 .. EIG_MAX_DIM, one workgroup
 // per block: T handed over by k_eigh_hh (orders up to HH_REG_DIM) or reduced
 // here in global memory.  Orders up to DC_MAX: divide and conquer on T, which
-// leaves the eigenvectors of T in u, its eigenvalues (unordered) in w and the
-// reflectors in a, for k_eigh_back and k_eigh_out.  Larger orders: Q formed,
+// leaves the eigenvectors of T in a, the reflectors in u and the order of the
+// eigenvalues on its diagonal, for k_eigh_back and k_eigh_out.  Larger orders: Q formed,
 // implicit QL on T applied to it, and the ordered output written here.
 __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *__restrict__ off,
                                                       const int32_t *__restrict__ dim, const int64_t *__restrict__ woff,
@@ -1116,7 +1133,7 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
     const int b = blockIdx.x;
     if (b >= nblk) return;
     const int d = dim[b];
-    if (d <= EIG_LDS_DIM || d > EIG_MAX_DIM) return;  // the Jacobi kernel's block (or rejected there)
+    if (d <= EIG_LDS_DIM || d > EIG_MAX_DIM) return;  // done (or rejected) by k_eigh_hh
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const size_t D = (size_t)d;
     double *A = u + off[b];  // working matrix (row-major, both triangles), then Householder vectors
@@ -1128,7 +1145,6 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
         for (int j = tid; j < d; j += TRI_TPB) {
             sd[j] = wb[j];
             se[j] = j + 1 < d ? A[(j + 1) * D + j] : 0.0;
-            if (j + 2 < d) sq[j] = A[(j + 2) * D + j];
         }
         __syncthreads();
     } else {
@@ -1290,18 +1306,37 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
     }
     if (d <= DC_MAX) {
         // the reflectors (rows of u beyond k + 1) and their factors t (at
-        // (k + 2, k)) to a, which the input no longer needs: k_eigh_back applies
-        // them to the eigenvectors of T; divide and conquer on T, its
-        // eigenvectors into u and its eigenvalues, unordered, into w
-        for (int k = wv; k + 2 < d; k += TRI_WAVES) {
-            for (int j = k + 2 + lane; j < d; j += 64) Z[k * D + j] = A[k * D + j];
-            if (lane == 0) Z[(k + 2) * D + k] = sq[k];
+        // (k + 2, k)) stay in u for k_eigh_back; divide and conquer on T, its
+        // eigenvectors into a, which the input no longer needs, its eigenvalues
+        // in descending order (ties by index) into w, and the index of the
+        // eigenvector that column c of the result takes into u(c, c)
+        if (d > HH_REG_DIM)
+            for (int k = tid; k + 2 < d; k += TRI_TPB) A[(k + 2) * D + k] = sq[k];
+        if (tid == 0) ctl[2] = 0;
+        __syncthreads();  // the factors in the pool are read up to here
+        dc_solve(d, sd, se, pool, (int *)srank, Z, red, ctl);
+        double *wb = w + woff[b];
+        for (int c = tid; c < d; c += TRI_TPB) {  // (values that are not numbers have no rank)
+            wb[c] = sd[c];
+            A[c * D + c] = c;
         }
         __syncthreads();
-        if (tid == 0) ctl[2] = 0;
-        dc_solve(d, sd, se, pool, (int *)srank, A, red, ctl);
-        double *wb = w + woff[b];
-        for (int i = tid; i < d; i += TRI_TPB) wb[i] = sd[i];
+        int G = 64;
+        while (G > 1 && G * d > TRI_TPB) G >>= 1;
+        if (64 * wv < G * d) {
+            const int i = min(tid / G, d - 1), g = tid & (G - 1);
+            const double wi = sd[i];
+            int above = 0;
+            for (int j = g; j < d; j += G) {
+                const double wj = sd[j];
+                above += (wj > wi) || (wj == wi && j < i);
+            }
+            const int rk = (int)group_sum((double)above, G);
+            if (tid / G < d && g == 0) {
+                wb[rk] = wi;
+                A[rk * D + rk] = i;
+            }
+        }
         if (tid == 0 && info) info[b] = ctl[2] ? -2 : 1 + ctl[3];
         return;
     }
@@ -1623,204 +1658,226 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
     if (tid == 0 && info) info[b] = bad ? -2 : 1 + its;
 }
 
-constexpr int BK_COLS = 16;                 // columns of a block per workgroup of k_eigh_back
+constexpr int BK_COLS = 16;                  // columns of a block per workgroup of k_eigh_back
 constexpr int BK_PANELS = DC_MAX / BK_COLS;  // its grid's second dimension
-constexpr int BK_TPB = 256;                  // four wavefronts of four columns
+constexpr int BK_TPB = 256;                  // four wavefronts
+constexpr int BK_LD = DC_MAX + 4;            // row stride of the staged reflectors (spreads the LDS banks)
+static_assert(QB == 16 && BK_TPB == 16 * QB && BK_COLS == 16, "sixteen reflectors by sixteen columns");
+
+// Apply the reflectors to the columns [cp, cp + 16) of Z, NT tiles of 16 rows a
+// wavefront (tile q = wave + 4 i), held in registers throughout in the layout in
+// which the matrix instruction leaves a product and takes its second operand.
+template <int NT>
+__device__ __forceinline__ void back_apply(int d, int cp, const double *__restrict__ H, double *__restrict__ Z,
+                                           double *sv, double *st, double (*red)[2][256]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane & 15, g = lane >> 4;
+    const size_t D = (size_t)d;
+    double *col = Z + (size_t)min(cp + c, d - 1) * D;
+    v4d_eig z[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = 16 * (wave + 4 * i) + 4 * v + g;
+            const double x = col[min(r, d - 1)];
+            z[i][v] = r < d ? x : 0.0;
+        }
+    // this thread's part of a block: reflector klo + kk, rows c + 16 j
+    const int kk = tid >> 4;
+    double pre[4 * NT], pt = 0.0;
+    auto fetch = [&](int khi) {
+        const int klo = max(0, khi - QB + 1), k = min(klo + kk, khi);
+#pragma unroll
+        for (int j = 0; j < 4 * NT; ++j)
+            if (16 * j + 15 > klo && 16 * j < d) pre[j] = H[(size_t)k * D + min(c + 16 * j, d - 1)];
+        pt = H[(size_t)(k + 2) * D + k];
+    };
+    if (d >= 3) fetch(d - 3);
+    for (int khi = d - 3; khi >= 0; khi -= QB) {
+        const int klo = max(0, khi - QB + 1), k = klo + kk;
+        const int q0 = (klo + 1) >> 4;  // first tile that the block reaches
+#pragma unroll
+        for (int j = 0; j < 4 * NT; ++j) {
+            const int r = c + 16 * j;
+            if (j >= q0 && 16 * j < d)
+                sv[kk * BK_LD + r] = k > khi || r > d - 1 || r < k + 1 ? 0.0 : (r == k + 1 ? 1.0 : pre[j]);
+        }
+        if (c == 0) st[kk] = k <= khi ? pt : 0.0;
+        __syncthreads();
+        if (khi - QB >= 0) fetch(khi - QB);
+        // Y = V^T Z and G = V^T V over this wavefront's rows
+        v4d_eig y4 = {0.0, 0.0, 0.0, 0.0}, g4 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const int q = wave + 4 * i;
+            if (q >= q0 && 16 * q < d) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const double x = sv[c * BK_LD + 16 * q + 4 * v + g];
+                    y4 = __builtin_amdgcn_mfma_f64_16x16x4f64(x, z[i][v], y4, 0, 0, 0);
+                    g4 = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, g4, 0, 0, 0);
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            red[wave][0][16 * (4 * v + g) + c] = y4[v];
+            red[wave][1][16 * (4 * v + g) + c] = g4[v];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) red[0][h][tid] = (red[0][h][tid] + red[1][h][tid]) + (red[2][h][tid] + red[3][h][tid]);
+        __syncthreads();
+        // H_klo ... H_khi Z = Z - V y, y_j = t_j (v_j.z - sum_{i > j} v_j.v_i y_i)
+        const double *Y = red[0][0], *G = red[0][1];
+        double y[QB];
+#pragma unroll
+        for (int j = 0; j < QB; ++j) y[j] = Y[16 * j + c];
+#pragma unroll
+        for (int j = QB - 1; j >= 0; --j) {
+            y[j] *= st[j];
+#pragma unroll
+            for (int i = 0; i < j; ++i) y[i] -= G[16 * j + i] * y[j];
+        }
+        double yb[4];  // the second operand of step s: -y[4 s + g]
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            yb[s] = -(g == 0 ? y[4 * s] : (g == 1 ? y[4 * s + 1] : (g == 2 ? y[4 * s + 2] : y[4 * s + 3])));
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const int q = wave + 4 * i;
+            if (q >= q0 && 16 * q < d) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    z[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(sv[(4 * s + g) * BK_LD + 16 * q + c], yb[s], z[i], 0, 0, 0);
+            }
+        }
+        __syncthreads();  // the next block restages sv and red
+    }
+    if (cp + c < d) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * (wave + 4 * i) + 4 * v + g;
+                if (r < d) col[r] = z[i][v];
+            }
+    }
+}
 
 // Eigenvectors of the divide-and-conquer blocks (orders EIG_LDS_DIM + 1 ..
-// DC_MAX): E = H_0 H_1 ... H_{d-3} Z, the reflectors (rows of a beyond k + 1,
-// t_k at a(k + 2, k)) applied to the eigenvectors Z of T (u, column-major),
-// the last one first.  Workgroup (b, p) owns columns [16 p, 16 p + 16) of
-// block b's Z and overwrites them with E: QB reflectors at a time are staged
-// in LDS (zero above each one's first row, 1 there), then each wavefront
-// applies them, two at a time, to four register-resident columns (one load
-// and one store of a column per QB reflectors).
+// DC_MAX): E = H_0 H_1 ... H_{d-3} Z, the reflectors (rows of u beyond k + 1,
+// t_k at u(k + 2, k)) applied to the eigenvectors Z of T (a, column-major), the
+// last one first, in place.  Workgroup (b, p) owns columns [16 p, 16 p + 16) of
+// block b.  Sixteen reflectors V at a time go through LDS (the next sixteen are
+// on their way meanwhile) and are applied at once: V^T Z and V^T V on FP64
+// MFMA, sixteen steps of substitution in every lane, Z - V y on FP64 MFMA.  The
+// chain of these blocks bounds it: 44 us at order 180, 211 at 512 (two reflectors
+// at a time with a reduction over the wavefront for each took 163 and 775).
 __global__ __launch_bounds__(BK_TPB) void k_eigh_back(int nblk, const int64_t *__restrict__ off,
-                                                      const int32_t *__restrict__ dim, const double *__restrict__ a,
-                                                      double *__restrict__ u) {
-    __shared__ double sv[QB * DC_MAX];  // [QB][L0]: the staged reflectors, rows r0..d-1
+                                                      const int32_t *__restrict__ dim, double *__restrict__ a,
+                                                      const double *__restrict__ u) {
+    __shared__ double sv[QB * BK_LD];
     __shared__ double st[QB];
-    __shared__ double ss[QB / 2];  // v_{k-1}.v_k of the pairs
+    __shared__ double red[BK_TPB / 64][2][256];
     const int b = blockIdx.x;
     if (b >= nblk) return;
     const int d = dim[b];
     if (d <= EIG_LDS_DIM || d > DC_MAX) return;
     const int cp = blockIdx.y * BK_COLS;
     if (cp >= d) return;
-    const size_t D = (size_t)d;
-    const double *H = a + off[b];
-    double *Z = u + off[b];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    for (int khi = d - 3; khi >= 0; khi -= QB) {
-        const int klo = max(0, khi - QB + 1), r0 = klo + 1, L0 = d - r0;
-        for (int i = threadIdx.x; i < (khi - klo + 1) * L0; i += blockDim.x) {
-            const int kk = i / L0, j = i - kk * L0, k = klo + kk, r = r0 + j;
-            sv[i] = r == k + 1 ? 1.0 : (r > k + 1 ? H[k * D + r] : 0.0);
-        }
-        for (int i = threadIdx.x; i <= khi - klo; i += blockDim.x) st[i] = H[(klo + i + 2) * D + klo + i];
-        __syncthreads();
-        // the reflectors go in pairs (k, k - 1) from khi down: s = v_{k-1}.v_k lets
-        // both products with a column be formed at once
-        const int npair = (khi - klo + 1) >> 1;
-        for (int pr = wave; pr < npair; pr += nw) {
-            const double *v1 = sv + (khi - 2 * pr - klo) * L0, *v2 = v1 - L0;
-            double part = 0.0;
-            for (int r = lane; r < L0; r += 64) part += v1[r] * v2[r];
-            part = group_sum<64>(part);
-            if (lane == 0) ss[pr] = part;
-        }
-        __syncthreads();
-        for (int c0 = cp + 4 * wave; c0 < min(d, cp + BK_COLS); c0 += 4 * nw) {
-            double cv[4][Q_REG];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const double *col = Z + (size_t)min(c0 + e, d - 1) * D + r0;
-#pragma unroll
-                for (int q = 0; q < Q_REG; ++q) {
-                    if (64 * q >= L0) break;  // uniform: the row slots past L0 are not used
-                    cv[e][q] = col[min(lane + 64 * q, L0 - 1)];
-                }
-            }
-            // H_{k-1} H_k c = c - t_k y1 v_k - t_{k-1} y2 v_{k-1}, y1 = v_k.c,
-            // y2 = v_{k-1}.c - t_k y1 s
-            for (int pr = 0; pr < npair; ++pr) {
-                const int k = khi - 2 * pr;
-                const double t1 = st[k - klo], t2 = st[k - 1 - klo], sp = ss[pr];
-                const double *v1 = sv + (k - klo) * L0, *v2 = v1 - L0;
-                double a1[4] = {0.0, 0.0, 0.0, 0.0}, a2[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int q = 0; q < Q_REG; ++q) {
-                    if (64 * q >= L0) break;
-                    const int r = lane + 64 * q;
-                    const double x1 = r < L0 ? v1[r] : 0.0, x2 = r < L0 ? v2[r] : 0.0;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        a1[e] += x1 * cv[e][q];
-                        a2[e] += x2 * cv[e][q];
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const double y1 = group_sum<64>(a1[e]), z = group_sum<64>(a2[e]);
-                    const double f1 = t1 * y1, f2 = t2 * (z - f1 * sp);
-#pragma unroll
-                    for (int q = 0; q < Q_REG; ++q) {
-                        if (64 * q >= L0) break;
-                        const int r = lane + 64 * q;
-                        if (r < L0) cv[e][q] -= f1 * v1[r] + f2 * v2[r];
-                    }
-                }
-            }
-            if (((khi - klo + 1) & 1) && st[0] != 0.0) {  // the block's last reflector, klo, alone
-                const double t = st[0];
-                const double *v = sv;
-                double acc[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int q = 0; q < Q_REG; ++q) {
-                    if (64 * q >= L0) break;
-                    const int r = lane + 64 * q;
-                    const double vr = r < L0 ? v[r] : 0.0;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[e] += vr * cv[e][q];
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const double ty = t * group_sum<64>(acc[e]);
-#pragma unroll
-                    for (int q = 0; q < Q_REG; ++q) {
-                        if (64 * q >= L0) break;
-                        const int r = lane + 64 * q;
-                        if (r < L0) cv[e][q] -= ty * v[r];
-                    }
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (c0 + e < d) {
-                    double *col = Z + (size_t)(c0 + e) * D + r0;
-#pragma unroll
-                    for (int q = 0; q < Q_REG; ++q) {
-                        const int r = lane + 64 * q;
-                        if (r < L0) col[r] = cv[e][q];
-                    }
-                }
-        }
-        __syncthreads();  // the next block restages sv
-    }
+    const double *H = u + off[b];
+    double *Z = a + off[b];
+    if (d <= 64)
+        back_apply<1>(d, cp, H, Z, sv, st, red);
+    else if (d <= 192)
+        back_apply<3>(d, cp, H, Z, sv, st, red);
+    else
+        back_apply<8>(d, cp, H, Z, sv, st, red);
 }
 
-// Output of the divide-and-conquer blocks: eigenvalues descending (ties by
-// index) into w, and the columns of E (u, column-major) in that order into u
-// (row-major), each with its first entry of largest magnitude positive; a is
-// the staging copy.
-__global__ __launch_bounds__(TRI_TPB) void k_eigh_out(int nblk, const int64_t *__restrict__ off,
-                                                      const int32_t *__restrict__ dim,
-                                                      const int64_t *__restrict__ woff, double *__restrict__ a,
-                                                      double *__restrict__ w, double *__restrict__ u) {
-    __shared__ double sv[DC_MAX], ssg[DC_MAX];
-    __shared__ int srk[DC_MAX], sinv[DC_MAX];
-    __shared__ double tile[32][33];
+constexpr int OUT_COLS = 32;  // columns of u per workgroup of k_eigh_out
+constexpr int OUT_TPB = 256;
+
+// Output of the divide-and-conquer blocks: the columns of E (a, column-major)
+// into u (row-major), column c the one whose index k_eigh_tri left at u(c, c),
+// with its first entry of largest magnitude positive.  Workgroup (b, p) owns
+// columns [32 p, 32 p + 32) of u, 32 x 32 tiles through LDS, read down the
+// columns of E and written along the rows of u: 13 us at order 180, a chain of
+// three reads (48 us with one workgroup per block and a staging copy).
+__global__ __launch_bounds__(OUT_TPB) void k_eigh_out(int nblk, const int64_t *__restrict__ off,
+                                                      const int32_t *__restrict__ dim, const double *__restrict__ a,
+                                                      double *__restrict__ u) {
+    constexpr int NC = OUT_COLS / (OUT_TPB / 64);  // columns of a wavefront
+    constexpr int NR = OUT_TPB / 32;               // rows of a tile at a time
+    __shared__ double ssg[OUT_COLS];
+    __shared__ int src[OUT_COLS];
+    __shared__ double tile[2][32][33];
     const int b = blockIdx.x;
     if (b >= nblk) return;
     const int d = dim[b];
     if (d <= EIG_LDS_DIM || d > DC_MAX) return;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
+    const int c0 = blockIdx.y * OUT_COLS;
+    if (c0 >= d) return;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const size_t D = (size_t)d;
-    const double *E = u + off[b];
-    double *S = a + off[b], *U = u + off[b], *wb = w + woff[b];
-    for (int i = tid; i < d; i += blockDim.x) sv[i] = wb[i];
-    __syncthreads();
-    for (int i = tid; i < d; i += blockDim.x) {
-        const double wi = sv[i];
-        int rank = 0;
-        for (int j = 0; j < d; ++j) {
-            const double wj = sv[j];
-            rank += (wj > wi) || (wj == wi && j < i);
-        }
-        srk[i] = rank;
+    const double *E = a + off[b];
+    double *U = u + off[b];
+    if (tid < OUT_COLS) {
+        const int c = min(c0 + tid, d - 1);
+        src[tid] = min(max((int)U[c * D + c], 0), d - 1);
     }
     __syncthreads();
-    for (int i = wv; i < d; i += nw) {
-        const double *col = E + i * D;
-        double best = -1.0;
-        int bi = 0;
-        for (int r = lane; r < d; r += 64) {
-            const double av = fabs(col[r]);
-            if (av > best) {
-                best = av;
-                bi = r;
+    double best[NC];
+    int bi[NC];  // twice the row, and the sign
+#pragma unroll
+    for (int e = 0; e < NC; ++e) {
+        best[e] = -1.0;
+        bi[e] = 0;
+    }
+    for (int r = lane; r < d; r += 64) {
+        double av[NC];
+#pragma unroll
+        for (int e = 0; e < NC; ++e) av[e] = E[src[NC * wv + e] * D + r];
+#pragma unroll
+        for (int e = 0; e < NC; ++e)
+            if (fabs(av[e]) > best[e]) {
+                best[e] = fabs(av[e]);
+                bi[e] = 2 * r + (av[e] < 0.0);
             }
-        }
+    }
+#pragma unroll
+    for (int e = 0; e < NC; ++e) {
         for (int o = 32; o > 0; o >>= 1) {
-            const double ob = __shfl_xor(best, o, 64);
-            const int oi = __shfl_xor(bi, o, 64);
-            if (ob > best || (ob == best && oi < bi)) {
-                best = ob;
-                bi = oi;
+            const double ob = __shfl_xor(best[e], o, 64);
+            const int oi = __shfl_xor(bi[e], o, 64);
+            if (ob > best[e] || (ob == best[e] && oi < bi[e])) {
+                best[e] = ob;
+                bi[e] = oi;
             }
         }
-        if (lane == 0) {
-            const int rk = srk[i];
-            ssg[rk] = col[bi] < 0.0 ? -1.0 : 1.0;
-            sinv[rk] = i;
-            wb[rk] = sv[i];
-        }
+        if (lane == 0) ssg[NC * wv + e] = (bi[e] & 1) ? -1.0 : 1.0;
     }
     __syncthreads();
-    // U(r, rk) = sign * E(r, i(rk)): 32 x 32 tiles through LDS, read down the
-    // columns of E and written along the rows of the staging copy
-    static_assert(TRI_TPB == 1024, "32 x 32 tile threads");
     const int tr = tid & 31, tc = tid >> 5;
-    for (int c0 = 0; c0 < d; c0 += 32)
-        for (int rr = 0; rr < d; rr += 32) {
-            const int rk = c0 + tc, r = rr + tr;
-            if (rk < d && r < d) tile[tc][tr] = ssg[rk] * E[(size_t)sinv[rk] * D + r];
-            __syncthreads();
-            const int r2 = rr + tc, rk2 = c0 + tr;
-            if (r2 < d && rk2 < d) S[(size_t)r2 * D + rk2] = tile[tr][tc];
-            __syncthreads();
+    double x[32 / NR];
+    auto fetch = [&](int rr) {
+#pragma unroll
+        for (int q = 0; q < 32 / NR; ++q) x[q] = E[src[tc + NR * q] * D + min(rr + tr, d - 1)];
+    };
+    fetch(0);
+    for (int rr = 0, h = 0; rr < d; rr += 32, h ^= 1) {
+#pragma unroll
+        for (int q = 0; q < 32 / NR; ++q) tile[h][tc + NR * q][tr] = ssg[tc + NR * q] * x[q];
+        __syncthreads();  // (the other buffer is read up to here: two are enough)
+        if (rr + 32 < d) fetch(rr + 32);
+#pragma unroll
+        for (int q = 0; q < 32 / NR; ++q) {
+            const int r = rr + tc + NR * q, c = c0 + tr;
+            if (r < d && c < d) U[r * D + c] = tile[h][tr][tc + NR * q];
         }
-    for (size_t e = tid; e < D * D; e += blockDim.x) U[e] = S[e];
+    }
 }
 
 // State selection (Alg. 1, step 7: a block keeps its states of largest
@@ -1961,11 +2018,10 @@ dmrg_status dmrg_eigh_blocks(int32_t nblk, const int64_t *off, const int32_t *di
     if (!off || !dim || !woff || !a || !w || !u) return set_error(DMRG_E_INVALID_ARG, "null argument");
     if (a == u || a == w || u == w) return set_error(DMRG_E_INVALID_ARG, "a, w and u must not overlap");
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_eigh_jacobi, dim3(nblk), dim3(EIG_TPB_SMALL), 0, s, nblk, off, dim, woff, a, w, u, info);
-    hipLaunchKernelGGL(k_eigh_hh, dim3(nblk), dim3(TRI_TPB), 0, s, nblk, off, dim, woff, a, w, u);
+    hipLaunchKernelGGL(k_eigh_hh, dim3(nblk), dim3(TRI_TPB), 0, s, nblk, off, dim, woff, (const double *)a, w, u, info);
     hipLaunchKernelGGL(k_eigh_tri, dim3(nblk), dim3(TRI_TPB), 0, s, nblk, off, dim, woff, a, w, u, info);
-    hipLaunchKernelGGL(k_eigh_back, dim3(nblk, BK_PANELS), dim3(BK_TPB), 0, s, nblk, off, dim, a, u);
-    hipLaunchKernelGGL(k_eigh_out, dim3(nblk), dim3(TRI_TPB), 0, s, nblk, off, dim, woff, a, w, u);
+    hipLaunchKernelGGL(k_eigh_back, dim3(nblk, BK_PANELS), dim3(BK_TPB), 0, s, nblk, off, dim, a, (const double *)u);
+    hipLaunchKernelGGL(k_eigh_out, dim3(nblk, DC_MAX / OUT_COLS), dim3(OUT_TPB), 0, s, nblk, off, dim, (const double *)a, u);
     DMRG_HIP(hipGetLastError());
     return DMRG_OK;
 }

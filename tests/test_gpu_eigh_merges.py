@@ -1,4 +1,6 @@
-"""The merges of the divide and conquer at the edges of their teams and tiles
+"""The reduction at the edges of its rows (60, 120 and 180 by four, eight and
+twelve rows a wavefront) and the merges of the divide and conquer at those of
+their teams and tiles
 (16 roots a panel, 96 or 64 rows a group; two panels a wavefront above order
 256), for spectra that deflate in different ways.  Tolerances as in the tests of
 the eigen-decomposition: 16 d u |A|_F."""
@@ -21,7 +23,8 @@ def _blocks(d, rng):
     return [_sym(rng, d), (clustered + clustered.T) / 2, (decaying + decaying.T) / 2, split, (glued + glued.T) / 2]
 
 
-@pytest.mark.parametrize("d", [9, 15, 16, 17, 31, 33, 63, 65, 95, 97, 127, 191, 193, 255, 256, 257, 289, 511])
+@pytest.mark.parametrize("d", [9, 15, 16, 17, 31, 33, 60, 61, 63, 65, 95, 97, 120, 121, 127, 179, 180, 181, 191,
+                               193, 255, 256, 257, 289, 511])
 def test_merge_edges(d):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
