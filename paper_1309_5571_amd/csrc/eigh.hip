@@ -14,7 +14,7 @@
 // 8 < d <= 2048: Householder reduction to tridiagonal form T = Q^T A Q (in
 // registers up to order 180, above in global memory, where the block stays
 // cache-resident), then T's eigenpairs.  Orders up to 512: Cuppen's divide and
-// conquer on T (leaves of at most 16 by implicit QL, one wavefront each; merges
+// conquer on T (leaves of 4 to 16 rows by implicit QL, one wavefront each; merges
 // by deflation, the secular equation on a group of lanes per root and Gu and
 // Eisenstat's recomputed weights), then the reflectors of Q applied to its
 // eigenvectors, 16 columns a workgroup.  Larger orders: Q formed, and the
@@ -400,15 +400,16 @@ __device__ __forceinline__ int ql_leaf(int m, double *d, double *e, double *Zl, 
 // Scratch of one merge (LDS, carved from the pool): doubles of length DC_MAX
 struct DcScratch {
     double *zz, *ds, *rc, *rs, *delta, *zeta, *tau, *zhat, *invn, *lamn;
-    int *perm, *defl, *rj, *ri, *nd, *tmp, *org;
+    int *perm, *defl, *rj, *ri, *nd, *tmp;
 };
 
 // The wavefronts that do one merge: 2^t merges of a level run side by side,
 // each on size = TRI_TPB >> t threads.  Every barrier is the workgroup's, so
 // all teams pass the same number of them.  A merge's time is a chain of
-// latencies (barriers, the root finder's iterations, one thread's deflation
-// scan) that more threads do not shorten; order 180, 15 merges one after the
-// other: 1.22 ms for the solve, four levels: 0.63 ms.
+// latencies (barriers, the root finder's iterations, the chains of
+// rotations) that more threads do not shorten; order 180, 15 merges one after the
+// other: 1.22 ms for the solve, four levels side by side: 0.63 ms, with smaller
+// leaves and the deflation scanned by a wavefront: 0.48 ms.
 struct DcTeam {
     int size, waves, tid, wv;  // wv: the wavefront's index in the team
 };
@@ -442,7 +443,7 @@ __device__ __forceinline__ int dc_rank(const double *v, int cnt, int i, int g, i
 // of rows.  The team holds the products of a group of rows in registers until
 // all of it has read them.  (One wavefront per two rows, a reciprocal for every
 // entry of W and pair of rows, was bound by them: order 512, 23.1 ms for the
-// whole solve against 16.8.)
+// whole solve against 16.9.)
 template <int NP, int RT>
 __device__ __forceinline__ void dc_rows(int n, int lo, int hi, int k, int mmax, double *Zt, const DcScratch &S,
                                         const DcTeam &tm) {
@@ -455,7 +456,7 @@ __device__ __forceinline__ void dc_rows(int n, int lo, int hi, int k, int mmax, 
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         const int j = min(16 * (tm.wv + p * tm.waves) + r16, max(k - 1, 0));
-        dj[p] = k > 0 ? dl[S.org[j]] : 0.0;
+        dj[p] = k > 0 ? S.zeta[j] : 0.0;
         tj[p] = k > 0 ? S.tau[j] : 0.0;
     }
     for (int c0 = 0; c0 < mmax; c0 += 16 * RT) {
@@ -555,66 +556,81 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, int mma
         }
     }
     __syncthreads();
-    // deflation (one thread, in pole order): a negligible weight leaves its pole;
-    // two poles closer than the resolution are rotated so that one weight vanishes.
-    // The poles and weights are read eight at a time; the pole kept from the last
-    // step (prev) is carried in registers, and the rotation test |(d_t - d_p) c s|
+    // deflation: a negligible weight leaves its pole; two poles closer than the
+    // resolution are rotated so that one weight vanishes, in pole order.  One
+    // wavefront: the weights and the neighbours are tested side by side, and only
+    // the chains of rotations that start at a close pair are followed one by one
+    // (a rotation changes the pole and weight that the next test takes; past the
+    // end of a chain the tests hold again).  The rotation test |(d_t - d_p) c s|
     // <= tol is taken as |d_t - d_p| |z_t z_p| <= tol (z_p^2 + z_t^2) (no root: the
-    // weights left are above tol / rh >= 8u, so the squares do not underflow).  A
-    // pole joins the list of kept ones once the next one can no longer deflate it.
-    if (tid == 0 && !on) ctl[0] = ctl[1] = 0;
-    if (tid == 0 && on) {
+    // weights left are above tol / rh >= 8u, so the squares do not underflow).
+    if (tm.wv == 0) {
+        const int lane = tid & 63;
+        const uint64_t below = (1ull << lane) - 1;
         double *zs = S.zeta, *ds = S.ds;
+        int *cand = S.nd;
         const double tol = 8.0 * 0x1p-53 * fmax(fmax(fabs(ds[0]), fabs(ds[m - 1])), rh);
-        int nrot = 0, prev = -1, k = 0;
-        double zp = 0.0, dp = 0.0;  // weight and pole of prev
-        for (int t0 = 0; t0 < m; t0 += 8) {
-            double zb[8], db[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int t = min(t0 + u, m - 1);
-                zb[u] = zs[t];
-                db[u] = ds[t];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int t = t0 + u;
-                if (t >= m) break;
-                double zt = zb[u], dt = db[u];
-                if (rh * fabs(zt) <= tol) {
-                    S.defl[t] = 1;
-                    continue;
-                }
-                S.defl[t] = 0;
-                bool rotated = false;
-                if (prev >= 0 && fabs(dt - dp) * fabs(zt * zp) <= tol * (zp * zp + zt * zt)) {
-                    const double tt = hyp(zp, zt);
-                    const double c = zt / tt, sn = -zp / tt;
+        auto close = [&](double zp, double dp, double zt, double dt) {
+            return fabs(dt - dp) * fabs(zt * zp) <= tol * (zp * zp + zt * zt);
+        };
+        int kc = 0, nrot = 0, k = 0;
+        for (int t0 = 0; on && t0 < m; t0 += 64) {
+            const int t = t0 + lane;
+            const bool keep = t < m && !(rh * fabs(zs[min(t, m - 1)]) <= tol);
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
+            if (t < m) S.defl[t] = !keep;
+            if (keep) cand[kc + __builtin_popcountll(mask & below)] = t;
+            kc += __builtin_popcountll(mask);
+        }
+        wave_sync_lds();
+        for (int i0 = 1, skip = 0; i0 < kc; i0 += 64) {
+            const int ii = min(i0 + lane, kc - 1), pp = cand[ii - 1], tt = cand[ii];
+            uint64_t mask = __builtin_amdgcn_ballot_w64(i0 + lane < kc && close(zs[pp], ds[pp], zs[tt], ds[tt]));
+            while (mask) {
+                int i = i0 + __builtin_ctzll(mask);
+                mask &= mask - 1;
+                if (i < skip) continue;  // in the last chain
+                int prev = cand[i - 1];
+                double zp = zs[prev], dp = ds[prev];
+                for (; i < kc; ++i) {
+                    const int t = cand[i];
+                    const double zt = zs[t], dt = ds[t];
+                    if (!close(zp, dp, zt, dt)) break;
+                    const double h = hyp(zp, zt);
+                    const double c = zt / h, sn = -zp / h;
                     const double dpn = dp * c * c + dt * sn * sn;
                     const double dtn = dp * sn * sn + dt * c * c;
-                    zs[t] = tt;
-                    zs[prev] = 0.0;
-                    ds[prev] = dpn;
-                    ds[t] = dtn;
-                    S.rj[nrot] = prev;
-                    S.ri[nrot] = t;
-                    S.rc[nrot] = c;
-                    S.rs[nrot] = sn;
+                    if (lane == 0) {
+                        zs[t] = h;
+                        zs[prev] = 0.0;
+                        ds[prev] = dpn;
+                        ds[t] = dtn;
+                        S.rj[nrot] = prev;
+                        S.ri[nrot] = t;
+                        S.rc[nrot] = c;
+                        S.rs[nrot] = sn;
+                        S.defl[prev] = 1;
+                    }
                     ++nrot;
-                    S.defl[prev] = 1;
-                    zt = tt;
-                    dt = dtn;
-                    rotated = true;
+                    prev = t;
+                    zp = h;
+                    dp = dtn;
                 }
-                if (prev >= 0 && !rotated) S.tmp[k++] = prev;  // prev is final
-                prev = t;
-                zp = zt;
-                dp = dt;
+                skip = i + 1;
             }
+            wave_sync_lds();
         }
-        if (prev >= 0) S.tmp[k++] = prev;
-        ctl[0] = k;
-        ctl[1] = nrot;
+        for (int i0 = 0; i0 < kc; i0 += 64) {
+            const int t = cand[min(i0 + lane, kc - 1)];
+            const bool keep = i0 + lane < kc && !S.defl[t];
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
+            if (keep) S.tmp[k + __builtin_popcountll(mask & below)] = t;
+            k += __builtin_popcountll(mask);
+        }
+        if (lane == 0) {
+            ctl[0] = k;
+            ctl[1] = nrot;
+        }
     }
     __syncthreads();
     const int k = ctl[0], nrot = ctl[1];
@@ -658,29 +674,13 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, int mma
         const bool last = j + 1 == k;
         const double lo_d = dl[j], hi_d = last ? dl[j] + rh * zsum : dl[j + 1];
         const double half = 0.5 * (hi_d - lo_d);
-        part = 0.0;
-        for (int i = g; i < k; i += G) part += zw[i] * zw[i] * rcpd(dl[i] - (lo_d + half));
-        const double f = 1.0 + rh * group_sum(part, G);
-        int o;
-        double a, bnd;
-        if (last || f >= 0.0) {
-            o = j;
-            a = 0.0;
-            bnd = last ? hi_d - lo_d : half;
-        } else {
-            o = j + 1;
-            a = -half;
-            bnd = 0.0;
-        }
-        const double dorg = dl[o];
-        const double dj = dl[j] - dorg, dj1 = last ? 0.0 : dl[j + 1] - dorg;
-        double x = 0.5 * (a + bnd);
-        bool done = false;
-        for (int it = 0; it < DC_ITMAX; ++it) {
-            if (__builtin_amdgcn_ballot_w64(!done) == 0) break;  // every root of the wavefront has stopped
-            double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;
+        // the sums over the poles below and above the gap at x from origin org
+        double psi, dpsi, phi, dphi;
+        auto sums = [&](double org, double x) {
+            psi = dpsi = phi = dphi = 0.0;
+#pragma unroll 4
             for (int i = g; i < k; i += G) {
-                const double r = rcpd((dl[i] - dorg) - x);
+                const double r = rcpd((dl[i] - org) - x);
                 const double t = zw[i] * zw[i] * r;
                 const bool below = i <= j;
                 psi += below ? t : 0.0;
@@ -692,6 +692,51 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, int mma
             dpsi = group_sum(dpsi, G);
             phi = group_sum(phi, G);
             dphi = group_sum(dphi, G);
+        };
+        // from x to the root of the model that the sums at x give.  (Its quotients
+        // by rcpd make single roots take twice the steps, and their wavefronts wait.)
+        auto model = [&](double dj, double dj1, double x, double bnd) {
+            const double u = dj - x, qq = dpsi * u * u, pp = psi - dpsi * u;
+            if (last) {
+                const double C = 1.0 + rh * (pp + phi);
+                return C != 0.0 ? dj + rh * qq / C : bnd;
+            }
+            const double v = dj1 - x, ss = dphi * v * v, rr = phi - dphi * v;
+            const double C = 1.0 + rh * (pp + rr), A1 = rh * qq, A2 = rh * ss;
+            // C (u - eta)(v - eta) + A1 (v - eta) + A2 (u - eta) = 0, root inside the gap
+            const double qb = -(C * (u + v) + A1 + A2), qc = C * u * v + A1 * v + A2 * u;
+            const double disc = qb * qb - 4.0 * C * qc;
+            const double sq = sqrt(fmax(disc, 0.0));
+            const double q1 = -0.5 * (qb + copysign(sq, qb));
+            const double e1 = q1 / C, e2 = qc / q1;
+            const double x1 = x + e1, x2 = x + e2;
+            return dj < x1 && x1 < dj1 ? x1 : x2;
+        };
+        sums(lo_d, half);
+        const double f = 1.0 + rh * (psi + phi);
+        int o;
+        double a, bnd, x;
+        if (last || f >= 0.0) {
+            o = j;
+            a = f >= 0.0 ? 0.0 : half;
+            bnd = f >= 0.0 ? half : hi_d - lo_d;
+            x = half;
+        } else {
+            o = j + 1;
+            a = -half;
+            bnd = 0.0;
+            x = -half;
+        }
+        const double dorg = dl[o];
+        const double dj = dl[j] - dorg, dj1 = last ? 0.0 : dl[j + 1] - dorg;
+        {
+            const double xn = model(dj, dj1, x, bnd);
+            x = (a < xn && xn < bnd) ? xn : 0.5 * (a + bnd);
+        }
+        bool done = false;
+        for (int it = 0; it < DC_ITMAX; ++it) {
+            if (__builtin_amdgcn_ballot_w64(!done) == 0) break;  // every root of the wavefront has stopped
+            sums(dorg, x);
             if (done) continue;
             const double fx = 1.0 + rh * (psi + phi);
             if (fx > 0.0)
@@ -703,31 +748,11 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, int mma
                 done = true;
                 continue;
             }
-            const double u = dj - x, qq = dpsi * u * u, pp = psi - dpsi * u;
-            double xn;
-            if (!last) {
-                const double v = dj1 - x, ss = dphi * v * v, rr = phi - dphi * v;
-                const double C = 1.0 + rh * (pp + rr), A1 = rh * qq, A2 = rh * ss;
-                // C (u - eta)(v - eta) + A1 (v - eta) + A2 (u - eta) = 0, root inside the gap
-                const double qb = -(C * (u + v) + A1 + A2), qc = C * u * v + A1 * v + A2 * u;
-                double eta;
-                if (C == 0.0) {
-                    eta = -qc / qb;
-                } else {
-                    const double sq = sqrt(fmax(qb * qb - 4.0 * C * qc, 0.0));
-                    const double q1 = -0.5 * (qb + copysign(sq, qb));
-                    const double e1 = q1 / C, e2 = q1 != 0.0 ? qc / q1 : e1;
-                    eta = (dj < x + e1 && x + e1 < dj1) ? e1 : e2;
-                }
-                xn = x + eta;
-            } else {
-                const double C = 1.0 + rh * (pp + phi);
-                xn = C != 0.0 ? dj + rh * qq / C : bnd;
-            }
+            const double xn = model(dj, dj1, x, bnd);
             x = (a < xn && xn < bnd) ? xn : 0.5 * (a + bnd);
         }
         if (jr < k && g == 0) {
-            S.org[j] = o;
+            S.zeta[j] = dorg;  // (the sorted z is not needed any more)
             S.tau[j] = x;
         }
     }
@@ -737,17 +762,20 @@ __device__ __forceinline__ void dc_merge(int n, int lo, int mid, int hi, int mma
     // norm) split the product (the sum) over the poles, as for the roots
     if (64 * tm.wv < G * k) {
         const int g = tid & (G - 1), ir = tid / G, i = min(ir, k - 1);
+        const double di = dl[i];
         double prod = 1.0;
+#pragma unroll 4
         for (int j = g; j < k; j += G)
-            if (j != i) prod *= ((dl[S.org[j]] - dl[i]) + S.tau[j]) * rcpd(dl[j] - dl[i]);
-        prod = group_prod(prod, G) * (((dl[S.org[i]] - dl[i]) + S.tau[i]) / rh);
+            if (j != i) prod *= ((S.zeta[j] - di) + S.tau[j]) * rcpd(dl[j] - di);
+        prod = group_prod(prod, G) * (((S.zeta[i] - di) + S.tau[i]) / rh);
         if (ir < k && g == 0) S.zhat[i] = copysign(sqrt(fmax(prod, 0.0)), zw[i]);
     }
     __syncthreads();
     if (64 * tm.wv < G * k) {
         const int g = tid & (G - 1), jr = tid / G, j = min(jr, k - 1);
-        const double dj = dl[S.org[j]], tj = S.tau[j];
+        const double dj = S.zeta[j], tj = S.tau[j];
         double q = 0.0;
+#pragma unroll 4
         for (int i = g; i < k; i += G) {
             const double x = S.zhat[i] * rcpd((dl[i] - dj) - tj);
             q += x * x;
@@ -808,16 +836,18 @@ __device__ __forceinline__ void dc_solve(int n, double *sd, double *se, double *
                                          double *red, int *ctl) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const size_t N = (size_t)n;
-    // leaves of at most 8 below order 65 (their QL chases are serial on one
-    // lane; measured faster there), of at most DC_LEAF above (fewer merges)
-    const int lmax = n <= 64 ? 8 : DC_LEAF;
+    // the smallest leaves (4 at most) that DC_NLEAF of them allow: their QL chases
+    // are serial on one lane, a level more of merges costs less (order 64, leaves
+    // of 8: 168 us, of 4: 135; order 128, of 16: 446, of 8: 332; order
+    // 180, of 16: 603, of 8: 483 with the merges as they were then)
+    const int lmax = n <= 4 * DC_NLEAF ? 4 : (n <= 8 * DC_NLEAF ? 8 : DC_LEAF);
     int T = 0;
     while (((n + (1 << T) - 1) >> T) > lmax) ++T;
     const int nleaf = 1 << T;
     auto bnd = [&](int t, int i) { return (n * i) >> t; };
     for (int c = wv; c < n; c += TRI_WAVES)
         for (int r = lane; r < n; r += 64) Zt[c * N + r] = 0.0;
-    // tear at the leaf boundaries (leaves hold at least 4 rows: no index is shared)
+    // tear at the leaf boundaries (leaves hold at least 2 rows: no index is shared)
     if (tid >= 1 && tid < nleaf) {
         const int b0 = bnd(T, tid);
         const double r = fabs(se[b0 - 1]);
@@ -878,8 +908,7 @@ __device__ __forceinline__ void dc_solve(int n, double *sd, double *se, double *
         S.ri = S.rj + DC_MAX;
         S.nd = S.ri + DC_MAX;
         S.tmp = S.nd + DC_MAX;
-        S.org = ipool + lo;
-        int *tctl = ipool + DC_MAX + 2 * i;
+        int *tctl = ipool + 2 * i;
         dc_merge(n, lo, mid, hi, (n + (1 << t) - 1) >> t, se[mid - 1], sd, Zt, S, tm, red, tctl);
     }
     if (tid == 0) ctl[3] += nleaf - 1;  // merges
