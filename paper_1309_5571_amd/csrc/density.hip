@@ -13,10 +13,9 @@
 #include <vector>
 
 #include "internal.h"
+#include "product.h"
 
 namespace dmrg {
-
-typedef double v4d_rho __attribute__((ext_vector_type(4)));
 
 // One 32x32 output tile (ti >= tj) of one block of rho.
 struct RhoTask {
@@ -25,21 +24,15 @@ struct RhoTask {
     int32_t ld;       // row length of Psi (d_R)
     int32_t dim;      // order of the rho block
     int32_t K;        // contraction length
-    int16_t side;     // 0: Psi Psi^T (left block), 1: Psi^T Psi (right block)
-    int16_t pad;
+    int32_t side;     // 0: Psi Psi^T (left block), 1: Psi^T Psi (right block)
     int32_t ti, tj;
 };
 
 constexpr int RHO_TILE = 32;
 
-// Element (r, k) of the contraction operand: side 0 reads Psi[r][k], side 1 Psi[k][r].
-__device__ __forceinline__ int64_t rho_index(int side, int ld, int r, int k) {
-    return side == 0 ? (int64_t)r * ld + k : (int64_t)k * ld + r;
-}
-
-// Four waves, one 16x16 quarter of the tile each.  Step j of a k-block of 16
-// takes k = k0 + 4 j + g (g = lane / 16), so steps past K are skipped.  The
-// loads are clamped to the block and zeroed after all of them are issued.
+// Four waves, one 16x16 quarter of the tile each (element (r, k) of the operand
+// is Psi[r][k] for the left block, Psi[k][r] for the right one).  The lanes past
+// the block's edge take its last row and are not written.
 __global__ __launch_bounds__(256) void k_density(const RhoTask *__restrict__ tasks, const double *__restrict__ psi,
                                                  double *__restrict__ rho_l, double *__restrict__ rho_r) {
     const RhoTask t = tasks[blockIdx.x];
@@ -49,28 +42,10 @@ __global__ __launch_bounds__(256) void k_density(const RhoTask *__restrict__ tas
     const int r16 = lane & 15, g = lane >> 4;
     const int r0 = t.ti * RHO_TILE + 16 * (wave >> 1), c0 = t.tj * RHO_TILE + 16 * (wave & 1);
     if (r0 >= t.dim || c0 >= t.dim || r0 + 15 < c0) return;  // outside, or above the diagonal
-    const double *X = psi + t.in_off;
-    const int ra = min(r0 + r16, t.dim - 1), cb = min(c0 + r16, t.dim - 1);
-    const bool oka = r0 + r16 < t.dim, okb = c0 + r16 < t.dim;
-    v4d_rho acc = {0.0, 0.0, 0.0, 0.0};
-    for (int k0 = 0; k0 < t.K; k0 += 16) {
-        double a[4], b[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int k = min(k0 + 4 * j + g, t.K - 1);
-            a[j] = X[rho_index(t.side, t.ld, ra, k)];
-            b[j] = X[rho_index(t.side, t.ld, cb, k)];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool kin = k0 + 4 * j + g < t.K;
-            a[j] = (oka && kin) ? a[j] : 0.0;
-            b[j] = (okb && kin) ? b[j] : 0.0;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (k0 + 4 * j < t.K) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j], b[j], acc, 0, 0, 0);
-    }
+    gptr X = (gptr)(psi + t.in_off);
+    const int64_t ra = min(r0 + r16, t.dim - 1), cb = min(c0 + r16, t.dim - 1);
+    const v4d_p acc = t.side == 0 ? tile_product<true, true>(X + ra * t.ld, 1, X + cb * t.ld, 1, t.K)
+                                  : tile_product<false, false>(X + ra, t.ld, X + cb, t.ld, t.K);
     // accumulator value v of lane (g, c) holds D[4 v + g][c]
     double *O = out + t.out_off;
 #pragma unroll
@@ -102,7 +77,7 @@ dmrg_status build_density(dmrg_plan *plan, hipStream_t s) {
                     t.ld = (int32_t)pr.dr;
                     t.dim = (int32_t)dim;
                     t.K = (int32_t)K;
-                    t.side = (int16_t)side;
+                    t.side = side;
                     t.ti = ti;
                     t.tj = tj;
                     tasks.push_back(t);

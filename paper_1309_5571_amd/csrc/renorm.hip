@@ -14,10 +14,9 @@
 #include <vector>
 
 #include "internal.h"
+#include "product.h"
 
 namespace dmrg {
-
-typedef double v4d_rn __attribute__((ext_vector_type(4)));
 
 // One 32x32 tile of C = op(A) B:  op(A)(i, k) = A[i lda + k], or A[k lda + i]
 // (trans), or (i == k) A[i] (diag, then K == M);  B(k, j) = B[k ldb + j].
@@ -45,32 +44,17 @@ __global__ __launch_bounds__(256) void k_gemm_tiles(const GemmTile *__restrict__
         }
         return;
     }
-    const int ra = min(r0 + r16, t.M - 1), cb = min(c0 + r16, t.N - 1);
-    const bool oka = r0 + r16 < t.M, okb = c0 + r16 < t.N;
-    v4d_rn acc = {0.0, 0.0, 0.0, 0.0};
-    for (int k0 = 0; k0 < t.K; k0 += 16) {
-        double a[4], b[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {  // clamped loads, all issued before any use
-            const int k = min(k0 + 4 * j + g, t.K - 1);
-            a[j] = t.mode == 1 ? t.A[(int64_t)k * t.lda + ra] : t.A[(int64_t)ra * t.lda + k];
-            b[j] = t.B[(int64_t)k * t.ldb + cb];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool kin = k0 + 4 * j + g < t.K;
-            a[j] = (oka && kin) ? a[j] : 0.0;
-            b[j] = (okb && kin) ? b[j] : 0.0;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (k0 + 4 * j < t.K) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j], b[j], acc, 0, 0, 0);
-    }
+    // the lanes past the edges take the last row or column and are not written
+    const int64_t ra = min(r0 + r16, t.M - 1), cb = min(c0 + r16, t.N - 1);
+    gptr A = (gptr)t.A, B = (gptr)t.B;
+    const v4d_p acc = t.mode == 1 ? tile_product<false, false>(A + ra, t.lda, B + cb, t.ldb, t.K)
+                                  : tile_product<true, false>(A + ra * t.lda, 1, B + cb, t.ldb, t.K);
+    auto C = (__attribute__((address_space(1))) double *)t.C;
     // accumulator value v of lane (g, c) holds D[4 v + g][c]
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int r = r0 + 4 * v + g, c = c0 + r16;
-        if (r < t.M && c < t.N) t.C[(int64_t)r * t.ldc + c] = acc[v];
+        if (r < t.M && c < t.N) C[(int64_t)r * t.ldc + c] = acc[v];
     }
 }
 
