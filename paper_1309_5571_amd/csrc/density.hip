@@ -31,21 +31,22 @@ struct RhoTask {
 constexpr int RHO_TILE = 32;
 
 // Four waves, one 16x16 quarter of the tile each (element (r, k) of the operand
-// is Psi[r][k] for the left block, Psi[k][r] for the right one).  The lanes past
-// the block's edge take its last row and are not written.
+// is Psi[r][k] for the left block, Psi[k][r] for the right one).
 __global__ __launch_bounds__(256) void k_density(const RhoTask *__restrict__ tasks, const double *__restrict__ psi,
                                                  double *__restrict__ rho_l, double *__restrict__ rho_r) {
     const RhoTask t = tasks[blockIdx.x];
     double *out = t.side == 0 ? rho_l : rho_r;
     if (!out) return;
+    __shared__ __align__(16) double lds[PANELS_LDS];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r16 = lane & 15, g = lane >> 4;
-    const int r0 = t.ti * RHO_TILE + 16 * (wave >> 1), c0 = t.tj * RHO_TILE + 16 * (wave & 1);
-    if (r0 >= t.dim || c0 >= t.dim || r0 + 15 < c0) return;  // outside, or above the diagonal
+    const int tr = t.ti * RHO_TILE, tc = t.tj * RHO_TILE;
     gptr X = (gptr)(psi + t.in_off);
-    const int64_t ra = min(r0 + r16, t.dim - 1), cb = min(c0 + r16, t.dim - 1);
-    const v4d_p acc = t.side == 0 ? tile_product<true, true>(X + ra * t.ld, 1, X + cb * t.ld, 1, t.K)
-                                  : tile_product<false, false>(X + ra, t.ld, X + cb, t.ld, t.K);
+    const Operand a = {X + (t.side == 0 ? (int64_t)tr * t.ld : tr), t.ld, t.dim - tr};
+    const Operand b = {X + (t.side == 0 ? (int64_t)tc * t.ld : tc), t.ld, t.dim - tc};
+    const v4d_p acc = t.side == 0 ? tile_product<true, true>(a, b, t.K, lds) : tile_product<false, false>(a, b, t.K, lds);
+    const int r0 = tr + 16 * (wave >> 1), c0 = tc + 16 * (wave & 1);
+    if (r0 >= t.dim || c0 >= t.dim || r0 + 15 < c0) return;  // outside, or above the diagonal
     // accumulator value v of lane (g, c) holds D[4 v + g][c]
     double *O = out + t.out_off;
 #pragma unroll

@@ -35,8 +35,8 @@ __global__ __launch_bounds__(256) void k_gemm_tiles(const GemmTile *__restrict__
     const GemmTile t = tiles[blockIdx.x];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r16 = lane & 15, g = lane >> 4;
-    const int r0 = t.ti * RN_TILE + 16 * (wave >> 1), c0 = t.tj * RN_TILE + 16 * (wave & 1);
-    if (r0 >= t.M || c0 >= t.N) return;
+    const int tr = t.ti * RN_TILE, tc = t.tj * RN_TILE;
+    const int r0 = tr + 16 * (wave >> 1), c0 = tc + 16 * (wave & 1);
     if (t.mode == 2) {  // C = diag(A) B: elementwise over the wave's quarter
         for (int e = lane; e < 256; e += 64) {
             const int r = r0 + (e >> 4), c = c0 + (e & 15);
@@ -44,11 +44,11 @@ __global__ __launch_bounds__(256) void k_gemm_tiles(const GemmTile *__restrict__
         }
         return;
     }
-    // the lanes past the edges take the last row or column and are not written
-    const int64_t ra = min(r0 + r16, t.M - 1), cb = min(c0 + r16, t.N - 1);
-    gptr A = (gptr)t.A, B = (gptr)t.B;
-    const v4d_p acc = t.mode == 1 ? tile_product<false, false>(A + ra, t.lda, B + cb, t.ldb, t.K)
-                                  : tile_product<true, false>(A + ra * t.lda, 1, B + cb, t.ldb, t.K);
+    __shared__ __align__(16) double lds[PANELS_LDS];
+    const Operand a = {(gptr)t.A + (t.mode == 1 ? tr : (int64_t)tr * t.lda), t.lda, t.M - tr};
+    const Operand b = {(gptr)t.B + tc, t.ldb, t.N - tc};
+    const v4d_p acc = t.mode == 1 ? tile_product<false, false>(a, b, t.K, lds) : tile_product<true, false>(a, b, t.K, lds);
+    if (r0 >= t.M || c0 >= t.N) return;
     auto C = (__attribute__((address_space(1))) double *)t.C;
     // accumulator value v of lane (g, c) holds D[4 v + g][c]
 #pragma unroll
