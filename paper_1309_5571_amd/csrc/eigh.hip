@@ -11,9 +11,9 @@
 // whole sub-blocks.  A sweep is d - 1 rounds (every pair once); the method
 // stops after a sweep with no rotation.
 //
-// 8 < d <= 2048: Householder reduction to tridiagonal form T = Q^T A Q (in
-// registers up to order 180, above in global memory, where the block stays
-// cache-resident), then T's eigenpairs.  Orders up to 512: Cuppen's divide and
+// 8 < d <= 2048: Householder reduction to tridiagonal form T = Q^T A Q (the last
+// 180 rows in registers, those before them in global memory, where the block
+// stays cache-resident), then T's eigenpairs.  Orders up to 512: Cuppen's divide and
 // conquer on T (leaves of 4 to 16 rows by implicit QL, one wavefront each; merges
 // by deflation, the secular equation on a group of lanes per root and Gu and
 // Eisenstat's recomputed weights), then the reflectors of Q applied to its
@@ -233,6 +233,7 @@ constexpr int HH_WAVES = TRI_WAVES - 1;       // wavefronts with rows of the blo
 constexpr int HH_REG_DIM = HH_WAVES * 4 * 3;  // largest order reduced there: 12 rows of three columns a thread
 constexpr int HH_VEC = 64 * 3;                // LDS vectors of that reduction
 static_assert(HH_REG_DIM <= HH_VEC, "vectors as long as the order");
+static_assert(5 * HH_VEC <= EIG_MAX_DIM && TRI_WAVES * HH_VEC <= 2 * EIG_MAX_DIM, "its LDS in the pool of the larger orders");
 static_assert(JAC_LDS <= TRI_TPB, "the Jacobi method in the partial products' place");
 
 // ------------------------------------------------------------------ divide and conquer
@@ -927,7 +928,8 @@ __device__ __forceinline__ void dc_solve(int n, double *sd, double *se, double *
 // leaves row k + 1 in srow; the wavefronts' partial products meet in LDS (spart)
 // as p = t A v, and w = p - K v goes next to v, the next step's pending update.
 // Each entry is updated by its own thread (A(i, j) and A(j, i) may differ by
-// roundings).
+// roundings).  D: the stride of the rows of Z, the block, and of A, which may be
+// the same; P0: the update (v', w') pending before step 0, zero past the order.
 // What bounds it: the LDS reads that every lane makes of a row's entries (one
 // serves NQ columns; with one column a thread they took most of a step) and the
 // chain of the scalars, which one wavefront does in the shortest time: with all
@@ -943,14 +945,12 @@ __device__ __forceinline__ double hh_pick(const double (&x)[NQ], int q) {  // x[
 }
 
 template <int NQ>
-__device__ __forceinline__ void hh_reduce(int d, const double *Z, double *A, double *wb, double2 *P0, double2 *P1,
-                                          double *srow, double *spart) {
+__device__ __forceinline__ void hh_reduce(int d, size_t D, const double *Z, double *A, double *wb, double2 *P0,
+                                          double2 *P1, double *srow, double *spart) {
     constexpr int R = 4 * NQ, LD = 64 * NQ;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // (so that the rows, and their tests, are scalar)
-    const size_t D = (size_t)d;
     for (int j = tid; j < HH_VEC; j += TRI_TPB) {
-        P0[j] = make_double2(0.0, 0.0);  // no update pending before step 0
         P1[j] = make_double2(0.0, 0.0);
         srow[j] = j < d ? Z[j] : 0.0;  // row 0
     }
@@ -1022,7 +1022,10 @@ __device__ __forceinline__ void hh_reduce(int d, const double *Z, double *A, dou
         const int G = (d + R - 1) / R;  // wavefronts that have rows
         double v[NQ], w[NQ], t = 0.0;   // the last step's reflector, the update pending before it
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) v[q] = w[q] = 0.0;
+        for (int q = 0; q < NQ; ++q) {
+            v[q] = cur[lane + 64 * q].x;
+            w[q] = cur[lane + 64 * q].y;
+        }
         // p = t A v, K = t p.v / 2, w = p - K v: step k's update, pending in buf
         auto update = [&](int k, double2 *buf) {
             double p[NQ], pv = 0.0;
@@ -1128,17 +1131,19 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_hh(int nblk, const int64_t *__
         eigh_jacobi(d, Z, wb, A, info ? info + b : nullptr, spart);
         return;
     }
+    for (int j = threadIdx.x; j < HH_VEC; j += TRI_TPB) P0[j] = make_double2(0.0, 0.0);  // no update is pending
     if (d <= HH_WAVES * 4)
-        hh_reduce<1>(d, Z, A, wb, P0, P1, srow, spart);
+        hh_reduce<1>(d, d, Z, A, wb, P0, P1, srow, spart);
     else if (d <= HH_WAVES * 8)
-        hh_reduce<2>(d, Z, A, wb, P0, P1, srow, spart);
+        hh_reduce<2>(d, d, Z, A, wb, P0, P1, srow, spart);
     else
-        hh_reduce<3>(d, Z, A, wb, P0, P1, srow, spart);
+        hh_reduce<3>(d, d, Z, A, wb, P0, P1, srow, spart);
 }
 
 // Tridiagonal path of the orders EIG_LDS_DIM + 1 .. EIG_MAX_DIM, one workgroup
 // per block: T handed over by k_eigh_hh (orders up to HH_REG_DIM) or reduced
-// here in global memory.  Orders up to DC_MAX: divide and conquer on T, which
+// here, in global memory as far as the block exceeds the registers (11 us a step
+// at order 256), the last HH_REG_DIM rows there (1.7): order 256, 3.12 -> 2.28 ms.  Orders up to DC_MAX: divide and conquer on T, which
 // leaves the eigenvectors of T in a, the reflectors in u and the order of the
 // eigenvalues on its diagonal, for k_eigh_back and k_eigh_out.  Larger orders: Q formed,
 // implicit QL on T applied to it, and the ordered output written here.
@@ -1242,7 +1247,8 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
             }
             __syncthreads();
         }
-        for (int k = 0; k + 2 < d; ++k) {
+        const int first = d - HH_REG_DIM;  // the block from here on is reduced in registers
+        for (int k = 0; k < first; ++k) {
             const int L = d - k - 1, G = max(1, min(TRI_TPB / L, 32));
             // p and w of step k (the groups' partial products meet in LDS)
             double pv = 0.0;
@@ -1258,9 +1264,9 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
             for (int j = tid; j < L; j += TRI_TPB) sy[j] -= K * sv[j];  // w
             __syncthreads();
             for (int j = 1 + tid; j < L; j += TRI_TPB) A[k * D + k + 1 + j] = sv[j];
+            if (k + 1 == first) break;  // its update is left pending
             // row k + 1 after step k's update (the same expression as for the
             // rest of the block): its diagonal, and the vector x of step k + 1 into sn
-            const bool next = k + 3 < d;
             double part = 0.0, diag = 0.0, lead = 0.0;
             for (int i = tid; i < L; i += TRI_TPB) {
                 const double val = A[(k + 1) * D + k + 1 + i] - __dadd_rn(__dmul_rn(sv[0], sy[i]), __dmul_rn(sy[0], sv[i]));
@@ -1272,12 +1278,7 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
             double alpha;  // x(0), handed over by the thread that formed it (sn[0] is rescaled below)
             const double sigma = block_sum1(part, tid == 1, lead, red2, &alpha);
             double tn = 0.0;
-            if (!next) {  // the trailing 2 x 2: no reflector
-                if (tid == 0) {
-                    sd[k + 1] = diag;
-                    se[k + 1] = alpha;
-                }
-            } else if (sigma == 0.0) {  // the column is already reduced
+            if (sigma == 0.0) {  // the column is already reduced
                 if (tid == 0) {
                     sd[k + 1] = diag;
                     se[k + 1] = alpha;
@@ -1296,8 +1297,8 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
                 }
             }
             __syncthreads();
-            // the rest of A22 (indices k + 2..): updated, stored, and (with a next
-            // step) summed into that step's p; thread (i, g) on the rows of group g
+            // the rest of A22 (indices k + 2..): updated, stored, and summed into the
+            // next step's p; thread (i, g) on the rows of group g
             // of column i, loads in batches
             const int L1 = L - 1, G1 = max(1, min(TRI_TPB / L1, 32)), R1 = (L1 + G1 - 1) / G1;
             for (int q = tid; q < G1 * L1; q += TRI_TPB) {
@@ -1320,7 +1321,7 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
                         }
                     }
                 }
-                if (next) spart[q] = acc;
+                spart[q] = acc;
             }
             __syncthreads();
             double *tmp = sv;  // the next step's v becomes the current one
@@ -1328,10 +1329,20 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
             sn = tmp;
             t = tn;
         }
-        if (tid == 0) {
-            sd[d - 1] = A[(d - 1) * D + d - 1];
-            se[d - 1] = 0.0;
+        // the last HH_REG_DIM rows and columns, with step first - 1's update
+        // pending, in registers (their vectors in the pool past the factors' t)
+        double2 *P0 = (double2 *)sx, *P1 = P0 + HH_VEC;
+        const double v0 = tid < HH_REG_DIM ? sv[tid] : 0.0, w0 = tid < HH_REG_DIM ? sy[tid] : 0.0;
+        __syncthreads();
+        if (tid < HH_VEC) P0[tid] = make_double2(v0, w0);
+        double *B = A + first * D + first;
+        hh_reduce<3>(HH_REG_DIM, D, B, B, sd + first, P0, P1, (double *)(P1 + HH_VEC), sy);
+        __syncthreads();
+        for (int j = first + tid; j < d; j += TRI_TPB) {
+            se[j] = j + 1 < d ? A[(j + 1) * D + j] : 0.0;
+            if (j + 2 < d) sq[j] = A[(j + 2) * D + j];
         }
+        __syncthreads();
     }
     if (d <= DC_MAX) {
         // the reflectors (rows of u beyond k + 1) and their factors t (at
