@@ -715,8 +715,11 @@ static void build_pass(const dmrg_plan *plan, bool adjoint, LowStore *low, uint6
     }
     int baseA = (int)hp.segs.size();
     hp.segs.insert(hp.segs.end(), segsA.begin(), segsA.end());
+    // (an FP64 pass that is not wide runs on the kernels of 16 x 16 tiles, whatever the
+    // tile table says of a block as small as an intermediate)
+    const int tsA = hp.wide || low ? hp.wide : 16;
     for (const TMat &tm : tmats)
-        add_tiles(hp.A, hp.wide, tm.rows, tm.cols, tm.off, 0, tm.cols, baseA + tm.seg, baseA + tm.seg + 1, 0, 0, tm.member);
+        add_tiles(hp.A, tsA, tm.rows, tm.cols, tm.off, 0, tm.cols, baseA + tm.seg, baseA + tm.seg + 1, 0, 0, tm.member);
     if (hp.wide) {
         for (std::vector<Task> *v : {&hp.A, &hp.B})
             for (Task &t : *v)
@@ -741,7 +744,7 @@ static dmrg_status upload(dmrg_plan *plan, const std::vector<T> &v, T **dst, hip
     return DMRG_OK;
 }
 
-static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, bool pack, hipStream_t s) {
+static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, bool low, bool pack, hipStream_t s) {
     if (pack) pack_tiles(hp, &ps.stageB.stride, &ps.stageB.dstride);
     // member-contiguous rows for the per-tile Rayleigh partials of stage B
     std::vector<int32_t> begin(plan->nprob + 1, 0), next;
@@ -760,6 +763,8 @@ static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, bool 
         if (t.m > 16 || t.n > 16) ps.stageA.ns = 2;
     for (const Task &t : hp.B)
         if (t.m > 16 || t.n > 16) ps.stageB.ns = 2;
+    if (!low && !hp.wide && (ps.stageA.ns != 1 || ps.stageB.ns != 1))
+        return set_error(DMRG_E_INVALID_ARG, "internal: a tile above 16 in a pass of 16 x 16 tiles");
     ps.wide = hp.wide;
     ps.small = hp.small;
     DMRG_TRY(upload(plan, hp.splitA, &ps.stageA.splits, s));
@@ -979,8 +984,8 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
             plan->d_partials = (double *)q;
         }
     }
-    DMRG_TRY(upload_pass(plan, f64, plan->fwd[0], true, stream));
-    DMRG_TRY(upload_pass(plan, a64, plan->adj[0], false, stream));
+    DMRG_TRY(upload_pass(plan, f64, plan->fwd[0], false, true, stream));
+    DMRG_TRY(upload_pass(plan, a64, plan->adj[0], false, false, stream));
     int64_t tmp = std::max(f64.tmp, a64.tmp);
 
     // ---- low-precision forward pass with converted operator copies
@@ -1004,7 +1009,7 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
         ConvJob *d_jobs = nullptr;
         DMRG_TRY(upload(plan, jobs, &d_jobs, stream));
         DMRG_TRY(launch_convert_jobs(d_jobs, (int)jobs.size(), prec, stream));
-        DMRG_TRY(upload_pass(plan, lo2, plan->fwd[1], prec == DMRG_F32, stream));
+        DMRG_TRY(upload_pass(plan, lo2, plan->fwd[1], true, prec == DMRG_F32, stream));
         tmp = std::max(tmp, lo2.tmp);
     }
     plan->tmp_bytes = std::max<int64_t>(tmp, 1) * 8;
