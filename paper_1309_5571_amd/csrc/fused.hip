@@ -51,10 +51,12 @@ __device__ __forceinline__ T load_at(gptr_of<T> base, uint32_t bytes) {
 }
 
 // Two-sided segment: for every 16-wide column sub-tile c of the intermediate,
-// T_c = A X_c (NS steps of the contraction at a time), then acc += T_c B_c^T.
+// T_c = A X_c (NS steps of the contraction at a time), then acc += T_c B_c^T;
+// in the adjoint pass T_c = A^T X_c and acc += T_c B_c, the same blocks read
+// along their other index.
 // With one piece (K <= 4 NS) A is loaded once and the loads of the next
 // sub-tile's X and B are issued before a sub-tile's products.
-template <int PREC, int NS, bool ONE>
+template <int PREC, bool ADJ, int NS, bool ONE>
 __device__ __forceinline__ void two_sided(typename Ft<PREC>::acc &acc, const Seg &s, const Task &tk, gptr in, int i,
                                           int g) {
     typedef typename Ft<PREC>::val V;
@@ -63,13 +65,14 @@ __device__ __forceinline__ void two_sided(typename Ft<PREC>::acc &acc, const Seg
     const gptr X = in + s.q;
     // byte offsets; contraction indices and columns are clamped to the last one
     const uint32_t row = tk.row0 + min(i, tk.m - 1), col = tk.col0 + min(i, tk.n - 1);
-    const uint32_t amax = (row * s.ldp + s.K - 1) * sizeof(V), xmax = (uint32_t)(s.K - 1) * s.ldq * 8u;
+    const uint32_t arow = ADJ ? row : row * s.ldp, ak = (ADJ ? s.ldp : 1) * (uint32_t)sizeof(V);
+    const uint32_t amax = arow * sizeof(V) + (s.K - 1) * ak, xmax = (uint32_t)(s.K - 1) * s.ldq * 8u;
     V a[NS], r[2][4];
     double x[2][NS];
     auto load_a = [&](int k0) {
-        const uint32_t o = (row * s.ldp + k0 + g) * sizeof(V);
+        const uint32_t o = arow * sizeof(V) + (k0 + g) * ak;
 #pragma unroll
-        for (int j = 0; j < NS; ++j) a[j] = load_at<V>(A, min(o + j * (uint32_t)(4 * sizeof(V)), amax));
+        for (int j = 0; j < NS; ++j) a[j] = load_at<V>(A, min(o + j * (4 * ak), amax));
     };
     auto load_x = [&](double (&to)[NS], int c, int k0) {
         const uint32_t xc = min(16 * c + i, s.K2 - 1) * 8u, o = (uint32_t)(k0 + g) * s.ldq * 8u;
@@ -78,8 +81,10 @@ __device__ __forceinline__ void two_sided(typename Ft<PREC>::acc &acc, const Seg
     };
     auto load_r = [&](V (&to)[4], int c) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            to[e] = load_at<V>(R, (col * s.ldr + min(16 * c + Ft<PREC>::row(g, e), s.K2 - 1)) * sizeof(V));
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t k = min(16 * c + Ft<PREC>::row(g, e), s.K2 - 1);
+            to[e] = load_at<V>(R, (ADJ ? k * s.ldr + col : col * s.ldr + k) * sizeof(V));
+        }
     };
     auto first = [&](A4 &t, const double (&xs)[NS], int rem) {
 #pragma unroll
@@ -226,14 +231,20 @@ __device__ __forceinline__ void diag_ahead(double (&v)[2], uint32_t dw, int n, c
         }
 }
 
-// The tile's product sums (modes as k_tasks, MODE 1): segment w, w + FW, ...
-// of the list on wavefront w, the wavefronts' sums added in order.  stride,
-// dstride: distance of consecutive tiles' descriptors, 0 if not packed.
-template <int PREC>
+// The tile's product sums: segment w, w + FW, ... of the list on wavefront w, the
+// wavefronts' sums added in order.  stride, dstride: distance of consecutive tiles'
+// descriptors, 0 if not packed.  ADJ: a tile of the adjoint; with GRAD also the
+// coefficient gradient's share <xg, segment product> of every segment and diagonal
+// term (out, and with it coef, may be null then).  Hubbard m = 2048, calls back to
+// back, us for the adjoint / the gradient / both in one pass: 8.2 / 14.3 / 14.9 against
+// 25.2 / 29.2 / 32.1 on 32 x 32 tiles (two launches; contractions below 16 value by
+// value) and 19.8 / 23.1 / 43.1 on the task kernel.
+template <int PREC, bool ADJ, bool GRAD>
 __global__ __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(2))) void k_fused(
     const Task *__restrict__ tasks, const Seg *__restrict__ segs, const DiagTerm *__restrict__ diags, int stride,
     int dstride, const double *__restrict__ in, const double *__restrict__ coef, const int32_t *__restrict__ mask,
-    const void *__restrict__ tmp, double *__restrict__ out, const double *__restrict__ dfold, RayArgs ray) {
+    const void *__restrict__ tmp, double *__restrict__ out, const double *__restrict__ dfold, RayArgs ray,
+    const double *__restrict__ xg, double *__restrict__ partials) {
     typedef typename Ft<PREC>::acc A4;
     __shared__ double red[FW][16][17];
     __shared__ double wtile[256];  // first the diagonal terms' sums, then the output values
@@ -260,13 +271,30 @@ __global__ __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(2))) vo
         pre_x = in[tk.x_off + o];
         pre_d = dfold[tk.c_off + o];
     }
+    // xg at this lane's elements of a product
+    double gx[4];
+    bool inside[4];
+    if (GRAD) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = Ft<PREC>::row(g, v);
+            inside[v] = r < tk.m && i < tk.n;
+            gx[v] = xg[tk.c_off + (int64_t)(tk.row0 + min(r, tk.m - 1)) * tk.ldc + tk.col0 + min(i, tk.n - 1)];
+        }
+    }
     double tot[4] = {0.0, 0.0, 0.0, 0.0};
     if (!stride && nseg > 0) {  // (a tile may have no segment, and a plan no descriptor at all)
         s = segs[tk.seg_begin + min(wave, nseg - 1)];
         next = segs[tk.seg_begin + min(wave + FW, nseg - 1)];
     }
     for (int si = wave; si < nseg; si += FW) {
-        const double c = (s.coef >= 0 ? coef[s.coef] : 1.0) * s.w;
+        const double c = GRAD && !out ? 0.0 : (s.coef >= 0 ? coef[s.coef] : 1.0) * s.w;
+        double part = 0.0;
+        auto add = [&](int v, double x) {
+            tot[v] += c * x;
+            // (outside the tile the product holds duplicated rows and columns, not zeros)
+            if (GRAD && inside[v]) part += gx[v] * x;
+        };
         A4 acc = {0, 0, 0, 0};
         if (s.fused == 2) {  // copy segment
             const gptr X = (gptr)in + s.q, vl = as_global(s.pscale), vr = as_global(s.qscale);
@@ -275,26 +303,43 @@ __global__ __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int64_t row = tk.row0 + min(Ft<PREC>::row(g, v), tk.m - 1);
-                tot[v] += c * (X[row * s.ldq + col] * (vl ? vl[row] : 1.0) * sc);
+                add(v, X[row * s.ldq + col] * (vl ? vl[row] : 1.0) * sc);
             }
         } else if (s.fused) {
             if (s.K <= 16)
-                two_sided<PREC, 4, true>(acc, s, tk, (gptr)in, i, g);
+                two_sided<PREC, ADJ, 4, true>(acc, s, tk, (gptr)in, i, g);
             else if (s.K <= 4 * LONG)
-                two_sided<PREC, LONG, true>(acc, s, tk, (gptr)in, i, g);
+                two_sided<PREC, ADJ, LONG, true>(acc, s, tk, (gptr)in, i, g);
             else
-                two_sided<PREC, LONG, false>(acc, s, tk, (gptr)in, i, g);
+                two_sided<PREC, ADJ, LONG, false>(acc, s, tk, (gptr)in, i, g);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) tot[v] += c * (double)acc[v];
+            for (int v = 0; v < 4; ++v) add(v, (double)acc[v]);
         } else {
             OneSided<PREC> one;
             one.load(s, tk, (gptr)in, tmp, i, g, 0);
             one.finish(acc, s, tk, (gptr)in, tmp, i, g);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) tot[v] += c * (double)acc[v];
+            for (int v = 0; v < 4; ++v) add(v, (double)acc[v]);
+        }
+        if (GRAD) {
+            part = group_sum<64>(part) * s.w;
+            if (lane == 0) partials[tk.part0 + si] = part;
         }
         s = next;
         next = segs[tk.seg_begin + min(si + 2 * FW, nseg - 1)];
+    }
+    if (GRAD) {
+        // diagonal terms: <xg, d v_l v_r in> over the tile, one wavefront per term
+        for (int d = tk.diag_begin + wave; d < tk.diag_end; d += FW) {
+            double part = 0.0;
+            for (int e = lane; e < cnt; e += 64) {
+                const int64_t rr = tk.row0 + e / tk.n, cc = tk.col0 + e % tk.n, o = rr * tk.ldc + cc;
+                part += diag_sum(diags, d, d + 1, nullptr, in[tk.x_off + o], rr, cc) * xg[tk.c_off + o];
+            }
+            part = group_sum<64>(part);
+            if (lane == 0) partials[tk.part0 + nseg + (d - tk.diag_begin)] = part;
+        }
+        if (!out) return;
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) red[wave][Ft<PREC>::row(g, v)][i] = tot[v];
@@ -352,17 +397,25 @@ __global__ __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
 }
 
-dmrg_status launch_fused(const PassSet &ps, int prec, const double *coef, const double *in, const void *tmp,
-                         double *out, hipStream_t s, const int32_t *mask, const double *dfold, const RayArgs *ray) {
+dmrg_status launch_fused(const PassSet &ps, int prec, bool adjoint, const double *coef, const double *in,
+                         const void *tmp, double *out, hipStream_t s, const int32_t *mask, const double *dfold,
+                         const RayArgs *ray, const double *xg, double *partials) {
     const Lists &l = ps.stageB;
     if (l.ntask) {
         const RayArgs ra = ray ? *ray : RayArgs{};
-        if (prec == DMRG_F64)
-            hipLaunchKernelGGL(k_fused<DMRG_F64>, dim3(l.ntask), dim3(64 * FW), 0, s, l.tasks, (const Seg *)ps.segs,
-                               (const DiagTerm *)ps.diags, l.stride, l.dstride, in, coef, mask, tmp, out, dfold, ra);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(l.ntask), dim3(64 * FW), 0, s, l.tasks, (const Seg *)ps.segs,
+                               (const DiagTerm *)ps.diags, l.stride, l.dstride, in, coef, mask, tmp, out, dfold, ra, xg,
+                               partials);
+        };
+        if (prec == DMRG_F32)
+            go(k_fused<DMRG_F32, false, false>);
+        else if (partials)
+            go(k_fused<DMRG_F64, true, true>);
+        else if (adjoint)
+            go(k_fused<DMRG_F64, true, false>);
         else
-            hipLaunchKernelGGL(k_fused<DMRG_F32>, dim3(l.ntask), dim3(64 * FW), 0, s, l.tasks, (const Seg *)ps.segs,
-                               (const DiagTerm *)ps.diags, l.stride, l.dstride, in, coef, mask, tmp, out, dfold, ra);
+            go(k_fused<DMRG_F64, false, false>);
     }
     DMRG_HIP(hipGetLastError());
     return DMRG_OK;

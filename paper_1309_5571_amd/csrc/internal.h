@@ -101,7 +101,8 @@ struct Task {
     int32_t row0, col0;
     int32_t m, n;      // rows / columns of this tile (<= tile size)
     int32_t member;
-    int32_t part0;     // adjoint output tiles: first partial slot of the tile's diagonal terms
+    int32_t part0;     // adjoint output tiles: first partial slot of the tile's diagonal terms (16 x 16
+                       // passes: of its segments, those of its diagonal terms after them)
     int32_t rslot;     // output-tile tasks: Rayleigh partial row (member-contiguous)
     int32_t nitem;     // wide passes: items of the tile's contraction (see Split)
     int32_t pad;
@@ -277,9 +278,11 @@ dmrg_status launch_diagonal(dmrg_plan *plan, const double *coef, double *diag, h
 constexpr int PROJ_NVEC = 4;
 dmrg_status launch_project_multi(dmrg_plan *plan, const double *coef, const double *in, int64_t in_stride,
                                  double *out, int64_t out_stride, const int32_t *vmask, hipStream_t s);
-// fused.hip: output tiles of a pass whose tiles all fit 16 x 16 (F64 or F32)
-dmrg_status launch_fused(const PassSet &ps, int prec, const double *coef, const double *in, const void *tmp,
-                         double *out, hipStream_t s, const int32_t *mask, const double *dfold, const RayArgs *ray);
+// fused.hip: output tiles of a pass whose tiles all fit 16 x 16 (F64 or F32; adjoint
+// passes F64).  xg, partials: as launch_tiles
+dmrg_status launch_fused(const PassSet &ps, int prec, bool adjoint, const double *coef, const double *in,
+                         const void *tmp, double *out, hipStream_t s, const int32_t *mask, const double *dfold,
+                         const RayArgs *ray, const double *xg = nullptr, double *partials = nullptr);
 // tiles.hip: a wide FP64 pass (both stages).  xg, partials: adjoint passes that
 // also form the coefficient-gradient partials <xg, segment product> (out may be null then)
 dmrg_status launch_tiles(const PassSet &ps, const double *coef, const double *in, double *tmp, double *out,

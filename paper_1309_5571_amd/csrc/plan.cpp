@@ -264,6 +264,14 @@ constexpr int64_t FUSE_MAX_K2 = 64;
 // 151, 120; 1227: 283, 181.  Members of m = 300 .. 512: 288 tiles 43, 41; 576: 75, 55.
 constexpr int64_t WIDE64_MIN = 320;
 
+// Adjoint passes take 16 x 16 tiles where the forward pass does and no block is above
+// this order.  Adjoint / gradient / both, us on 16 x 16 against 32 x 32 tiles: Hubbard
+// m = 2048 (order 36) 8 / 14 / 15 against 25 / 29 / 32, Heisenberg m = 512 (90) 15 / 17 / 18
+// against 17 / 24 / 25, Hubbard m = 5120 (90) 57 / 75 / 79 against 59 / 71 / 77, m = 6144
+// (108) 82 / 104 / 110 against 71 / 88 / 96, Heisenberg m = 1024 (180) 31 / 38 / 39
+// against 24 / 33 / 34.
+constexpr int64_t ADJ16_MAX = 96;
+
 // Tiles of side ts (0: by the tile table) of one output matrix.
 static void add_tiles(std::vector<Task> &out, int ts, int64_t rows, int64_t cols, int64_t c_off, int64_t x_off,
                       int64_t ld, int32_t seg_b, int32_t seg_e, int32_t d_b, int32_t d_e, int member) {
@@ -435,6 +443,25 @@ static void make_splits(int TW, std::vector<Task> &tasks, const std::vector<Seg>
     if (npart) *npart = part;
 }
 
+// Coefficient-gradient partials of an adjoint pass: their slots, their number and
+// the slots of each term.  16 x 16 tiles: one per segment of the tile, then one per
+// diagonal term.
+static void gradient_slots(HostPass &hp, std::vector<std::vector<int32_t>> &per_term, int32_t *npart) {
+    if (hp.wide) {
+        make_splits(TWB, hp.B, hp.segs, hp.splitB, &hp.diags, &per_term, npart);
+        return;
+    }
+    int32_t part = 0;
+    for (Task &t : hp.B) {
+        t.part0 = part;
+        for (int s = t.seg_begin; s < t.seg_end; ++s, ++part)
+            if (hp.segs[s].term >= 0) per_term[hp.segs[s].term].push_back(part);
+        for (int d = t.diag_begin; d < t.diag_end; ++d, ++part)
+            if (hp.diags[d].term >= 0) per_term[hp.diags[d].term].push_back(part);
+    }
+    *npart = part;
+}
+
 // Low-precision copies of operator blocks: (op, blk, variant) -> device address.
 struct LowStore {
     struct Job {
@@ -471,18 +498,18 @@ static void build_pass(const dmrg_plan *plan, bool adjoint, LowStore *low, uint6
         const Record &rc = plan->records[r];
         by_out[adjoint ? rc.oin : rc.oout].push_back(r);
     }
-    // FP64 passes with a tile wider than 16, and every adjoint pass, run on the wide
-    // tiles; reduced precisions and all-16 forward passes (whose two-sided records
-    // fuse into one launch) keep the kernels of project.hip.  A tile table of one
+    // FP64 passes with a tile wider than 16 run on the wide tiles; all-16 ones, whose
+    // two-sided records fuse into one launch, on fused.hip (intermediates too wide for
+    // that: project.hip), reduced precisions there and on project.hip.  A tile table of one
     // class asks for one tile size whatever else is in the plan (a member's result is
     // then the same bits alone and in a batch): no 64 x 64 tiles there.
     for (const Geo &g : plan->out_geo) hp.small = hp.small && g.rows * g.ld < (int64_t)1 << 28;
     for (const Record &rc : plan->records)
         for (const OpBlock *b : {&rc.a, &rc.b}) hp.small = hp.small && b->rows * b->cols < (int64_t)1 << 28;
     if (!low) {
-        hp.wide = adjoint || !hp.small ? 32 : 0;
+        hp.wide = !hp.small ? 32 : 0;
         for (const Geo &g : plan->out_geo)
-            if (tile_for(g.rows, g.cols) > 16) hp.wide = 32;
+            if (tile_for(g.rows, g.cols) > 16 || (adjoint && std::max(g.rows, g.cols) > ADJ16_MAX)) hp.wide = 32;
         int64_t n64 = 0;
         for (const Geo &g : plan->out_geo) n64 += ((g.rows + 63) / 64) * ((g.cols + 63) / 64);
         if (hp.wide && !adjoint && g_ncls != 1 && n64 >= WIDE64_MIN) hp.wide = 64;
@@ -656,6 +683,20 @@ static void build_pass(const dmrg_plan *plan, bool adjoint, LowStore *low, uint6
                     s.qtrans = 0;
                     s.ldq = (int32_t)dk;
                     s.K = (int32_t)dl;
+                    hp.segs.push_back(s);
+                } else if (!hp.wide && dl <= FUSE_MAX_K2) {  // as forward, both blocks along their other index
+                    s.fused = 1;
+                    s.p = U(rc.a.data);
+                    s.pkind = OPD_ABS;
+                    s.ptrans = 1;
+                    s.ldp = (int32_t)di;
+                    s.q = (uint64_t)gi.off;
+                    s.qkind = OPD_IN;
+                    s.ldq = (int32_t)gi.ld;
+                    s.K = (int32_t)dj;
+                    s.r = U(rc.b.data);
+                    s.ldr = (int32_t)dk;
+                    s.K2 = (int32_t)dl;
                     hp.segs.push_back(s);
                 } else {
                     Seg a{};
@@ -914,8 +955,7 @@ static void scratch_sizes(const dmrg_plan *plan, int32_t prec, int64_t *tmp, int
     int64_t t = std::max(f64.tmp, a64.tmp);
     int32_t part = 0;
     std::vector<std::vector<int32_t>> per_term(plan->nterm_total);
-    std::vector<Split> splits;
-    make_splits(TWB, a64.B, a64.segs, splits, &a64.diags, &per_term, &part);
+    gradient_slots(a64, per_term, &part);
     int32_t tl = std::max<int32_t>(1, (int32_t)f64.B.size());
     if (prec != DMRG_F64) {
         LowStore ls;
@@ -960,12 +1000,12 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
         make_splits(TWA, f64.A, f64.segs, f64.splitA, nullptr, nullptr, nullptr);
         make_splits(TWB, f64.B, f64.segs, f64.splitB, nullptr, nullptr, nullptr);
     }
-    make_splits(TWA, a64.A, a64.segs, a64.splitA, nullptr, nullptr, nullptr);
+    if (a64.wide) make_splits(TWA, a64.A, a64.segs, a64.splitA, nullptr, nullptr, nullptr);
     // coefficient-gradient partial slots (adjoint stage B)
     {
         int32_t part = 0;
         std::vector<std::vector<int32_t>> per_term(plan->nterm_total);
-        make_splits(TWB, a64.B, a64.segs, a64.splitB, &a64.diags, &per_term, &part);
+        gradient_slots(a64, per_term, &part);
         std::vector<int32_t> ptr(1, 0), ent;
         for (auto &v : per_term) {
             ent.insert(ent.end(), v.begin(), v.end());
@@ -985,7 +1025,7 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
         }
     }
     DMRG_TRY(upload_pass(plan, f64, plan->fwd[0], false, true, stream));
-    DMRG_TRY(upload_pass(plan, a64, plan->adj[0], false, false, stream));
+    DMRG_TRY(upload_pass(plan, a64, plan->adj[0], false, true, stream));
     int64_t tmp = std::max(f64.tmp, a64.tmp);
 
     // ---- low-precision forward pass with converted operator copies

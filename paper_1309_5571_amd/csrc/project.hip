@@ -1055,13 +1055,14 @@ static void launch_tasks(const Lists &l, size_t lds, hipStream_t s, Args... args
 }
 
 template <int PREC>
-static dmrg_status run_pass(const PassSet &ps, const double *coef, const double *in, void *tmp, double *out,
-                            hipStream_t s, const int32_t *mask, const double *dfold, const RayArgs *ray) {
+static dmrg_status run_pass(const PassSet &ps, bool adjoint, const double *coef, const double *in, void *tmp,
+                            double *out, hipStream_t s, const int32_t *mask, const double *dfold, const RayArgs *ray,
+                            const double *xg = nullptr, double *partials = nullptr) {
     if (ps.stageA.ntask)
         launch_tasks<PREC, 0>(ps.stageA, TASK_LDS, s, (const Seg *)ps.segs, (const DiagTerm *)ps.diags, in,
                               (const void *)tmp, tmp, coef, mask, (const double *)nullptr, RayArgs{});
     if (PREC == DMRG_F64 || (PREC == DMRG_F32 && ps.stageB.ns == 1 && ps.small))
-        return launch_fused(ps, PREC, coef, in, tmp, out, s, mask, dfold, ray);
+        return launch_fused(ps, PREC, adjoint, coef, in, tmp, out, s, mask, dfold, ray, xg, partials);
     if constexpr (PREC != DMRG_F64) if (ps.stageB.ntask) {
         const RayArgs ra = ray ? *ray : RayArgs{};
         launch_tasks<PREC, 1>(ps.stageB, TASK_LDS, s, (const Seg *)ps.segs, (const DiagTerm *)ps.diags, in,
@@ -1075,14 +1076,23 @@ dmrg_status launch_project(dmrg_plan *plan, int slot, const double *coef, const 
                            hipStream_t s, const int32_t *mask, const double *dfold, const RayArgs *ray) {
     if (slot == 0 && plan->fwd[0].wide)
         return launch_tiles(plan->fwd[0], coef, in, (double *)plan->d_tmp, out, s, mask, dfold, ray);
-    if (slot == 0) return run_pass<DMRG_F64>(plan->fwd[0], coef, in, plan->d_tmp, out, s, mask, dfold, ray);
+    if (slot == 0) return run_pass<DMRG_F64>(plan->fwd[0], false, coef, in, plan->d_tmp, out, s, mask, dfold, ray);
     if (plan->prec == DMRG_F32)
-        return run_pass<DMRG_F32>(plan->fwd[1], coef, in, plan->d_tmp, out, s, mask, dfold, ray);
-    return run_pass<DMRG_BF16>(plan->fwd[1], coef, in, plan->d_tmp, out, s, mask, dfold, ray);
+        return run_pass<DMRG_F32>(plan->fwd[1], false, coef, in, plan->d_tmp, out, s, mask, dfold, ray);
+    return run_pass<DMRG_BF16>(plan->fwd[1], false, coef, in, plan->d_tmp, out, s, mask, dfold, ray);
+}
+
+// The adjoint pass; xg, partials: see launch_tiles.
+static dmrg_status adjoint_pass(dmrg_plan *plan, const double *coef, const double *in, double *out, hipStream_t s,
+                                const double *xg, double *partials) {
+    const PassSet &ps = plan->adj[0];
+    if (ps.wide)
+        return launch_tiles(ps, coef, in, (double *)plan->d_tmp, out, s, nullptr, nullptr, nullptr, xg, partials);
+    return run_pass<DMRG_F64>(ps, true, coef, in, plan->d_tmp, out, s, nullptr, nullptr, nullptr, xg, partials);
 }
 
 dmrg_status launch_adjoint(dmrg_plan *plan, const double *coef, const double *in, double *out, hipStream_t s) {
-    return launch_tiles(plan->adj[0], coef, in, (double *)plan->d_tmp, out, s, nullptr, nullptr, nullptr);
+    return adjoint_pass(plan, coef, in, out, s, nullptr, nullptr);
 }
 
 dmrg_status launch_diag_fold(dmrg_plan *plan, int slot, const double *coef, double *out, hipStream_t s) {
@@ -1099,8 +1109,7 @@ dmrg_status launch_gcoef(dmrg_plan *plan, const double *coef, const double *psi,
     // gcoef_k = <gbar, T_k psi> = <psi, T_k^T gbar>: the segment products the
     // adjoint pass forms anyway, each multiplied by its tile of psi
     if (plan->d_partials)
-        DMRG_TRY(launch_tiles(plan->adj[0], coef, gbar, (double *)plan->d_tmp, gpsi, s, nullptr, nullptr, nullptr,
-                              psi, plan->d_partials));
+        DMRG_TRY(adjoint_pass(plan, coef, gbar, gpsi, s, psi, plan->d_partials));
     else if (gpsi)
         DMRG_TRY(launch_adjoint(plan, coef, gbar, gpsi, s));
     if (plan->nterm_total)
