@@ -540,8 +540,8 @@ dmrg_status dmrg_plan_create_l11r(dmrg_plan **out, int32_t nprob, const dmrg_pro
 /* Set the tile table used by later dmrg_plan_create calls: for output
  * blocks with max(rows, cols) <= bound[c] (ascending, ncls <= 8), tiles of
  * tile[c] rows and columns (16 or 32).  ncls = 0 restores the built-in table.
- * FP64 passes with any tile of 32 use 32 for every block, and 64 in plans of
- * 320 or more such tiles unless the table has a single class.
+ * FP64 passes with any tile of 32 use 32 for every block, and 64 in plans with
+ * work for some 200 such tiles or more unless the table has a single class.
  * Process-wide; not thread-safe against concurrent plan creation. */
 dmrg_status dmrg_set_tile_table(int32_t ncls, const int32_t *bound, const int32_t *tile);
 

@@ -259,10 +259,17 @@ static uint64_t U(const void *p) { return (uint64_t)(uintptr_t)p; }
 // Largest intermediate width a fused two-sided segment keeps in LDS (16 rows x 64).
 constexpr int64_t FUSE_MAX_K2 = 64;
 
-// 64 x 64 tiles from this many of them on.  Members of m = 256 .. 1536: 173 tiles
-// 60 us with 32 x 32 tiles, 84 us with 64 x 64; 320: 90, 91; 472: 123, 106; 627:
-// 151, 120; 1227: 283, 181.  Members of m = 300 .. 512: 288 tiles 43, 41; 576: 75, 55.
-constexpr int64_t WIDE64_MIN = 320;
+// 64 x 64 tiles from this many of the longest contraction on.  One such tile sets
+// the time that a pass on them takes at least (four wavefronts against eight and a
+// quarter of the tiles), so the others count by their contraction, start and end of
+// a tile as eight items.  Projection on 32 x 32 and on 64 x 64 tiles, us, at counts of
+//   52: 17.9, 35.1 (8 members of m = 32 .. 512)        112: 32.5, 59.0 (31 of m = 32 .. 62
+//   and one of 1024; 388 tiles of any length)          139: 96.8, 114 (m = 2048)
+//   177: 86.1, 87.4 (8 of 256 .. 1536)                 181: 41.3, 39.8 (16 of 300 .. 512)
+//   197: 35.9, 37.8 (32 of 32 .. 512)                  225: 102, 94.3 (16 of 64 .. 1536)
+//   248: 112, 92.8 (Hubbard m = 8192)                  272: 209, 225 (m = 3072)
+//   340: 143, 114 (16 of 256 .. 1536)                  1815: 1010, 568 (64 of 256 .. 2048)
+constexpr double WIDE64_MIN = 200.0;
 
 // Adjoint passes take 16 x 16 tiles where the forward pass does and no block is above
 // this order.  Adjoint / gradient / both, us on 16 x 16 against 32 x 32 tiles: Hubbard
@@ -462,6 +469,23 @@ static void gradient_slots(HostPass &hp, std::vector<std::vector<int32_t>> &per_
     *npart = part;
 }
 
+// 64 x 64 output tiles of the forward pass, in tiles of the longest contraction (see WIDE64_MIN).
+static double tiles64(const dmrg_plan *plan) {
+    std::vector<int64_t> items(plan->out_geo.size(), 8);
+    for (const Record &rc : plan->records) {
+        const bool da = rc.a.kind == DMRG_OP_DENSE, db = rc.b.kind == DMRG_OP_DENSE;
+        const int64_t K = da && (!db || rc.order == 1) ? rc.gin.rows : (db ? rc.gin.cols : 0);
+        items[rc.oout] += (K + 15) / 16;
+    }
+    double work = 0.0, longest = 8.0;
+    for (size_t q = 0; q < items.size(); ++q) {
+        const Geo &g = plan->out_geo[q];
+        work += (double)(((g.rows + 63) / 64) * ((g.cols + 63) / 64) * items[q]);
+        longest = std::max(longest, (double)items[q]);
+    }
+    return work / longest;
+}
+
 // Low-precision copies of operator blocks: (op, blk, variant) -> device address.
 struct LowStore {
     struct Job {
@@ -510,9 +534,7 @@ static void build_pass(const dmrg_plan *plan, bool adjoint, LowStore *low, uint6
         hp.wide = !hp.small ? 32 : 0;
         for (const Geo &g : plan->out_geo)
             if (tile_for(g.rows, g.cols) > 16 || (adjoint && std::max(g.rows, g.cols) > ADJ16_MAX)) hp.wide = 32;
-        int64_t n64 = 0;
-        for (const Geo &g : plan->out_geo) n64 += ((g.rows + 63) / 64) * ((g.cols + 63) / 64);
-        if (hp.wide && !adjoint && g_ncls != 1 && n64 >= WIDE64_MIN) hp.wide = 64;
+        if (hp.wide && !adjoint && g_ncls != 1 && tiles64(plan) >= WIDE64_MIN) hp.wide = 64;
     }
     auto blk_addr = [&](const OpBlock &b, int variant) -> uint64_t {
         if (!low) return U(b.data);

@@ -43,3 +43,22 @@ def test_intermediates_of_the_wider_class(a, b):
     gpsi, gcoef = (t.cpu().numpy() for t in plan.backward_raw(dev(X[0]), dev(g)))
     assert close(gpsi, projection.project_adjoint_sectors(p, g))
     assert close(gcoef, projection.coef_gradient(p, X[0], g))
+
+
+def test_mixed_batch():
+    """One large member and many small ones: more than 320 tiles of 64 x 64 by their
+    number, but the work of far fewer (the plan keeps the smaller tiles); every member
+    against its own oracle."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gen
+    import paper_1309_5571_amd as dm
+
+    probs = [gen.heisenberg_synthetic(m, seed=600 + m) for m in range(32, 62)] + [gen.heisenberg_synthetic(700, seed=9)]
+    plan = dm.Plan(probs, tiles=None)
+    x = np.random.default_rng(4).standard_normal(plan.n)
+    y = plan.project_raw(torch.from_numpy(x).cuda()).cpu().numpy()
+    mo = plan.member_off
+    for i, p in enumerate(probs):
+        ref = projection.project_sectors(p, x[mo[i]:mo[i + 1]])
+        assert np.linalg.norm(y[mo[i]:mo[i + 1]] - ref) <= 1e-12 * np.linalg.norm(ref), i
