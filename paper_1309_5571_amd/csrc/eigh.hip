@@ -40,6 +40,12 @@ constexpr int TRI_TPB = 1024;  // tridiagonal path
 constexpr int TRI_WAVES = TRI_TPB / 64;
 constexpr int QL_MAXIT = 60;  // QL iterations per eigenvalue before the block is reported unconverged
 
+// LDS writes of a wavefront's lanes are visible to its other lanes after it
+__device__ __forceinline__ void wave_sync_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Pair k of round r of the circle ordering on n' = m + 1 (even) indices:
 // k = 0 pairs r with the fixed index m, k > 0 pairs r + k with r - k (mod m).
 __device__ __forceinline__ void circle_pair(int r, int k, int m, int &p, int &q) {
@@ -52,26 +58,27 @@ __device__ __forceinline__ void circle_pair(int r, int k, int m, int &p, int &q)
     }
 }
 
-// One block of order d <= EIG_LDS_DIM, by the whole workgroup; lds: JAC_LDS doubles.
+// One block of order d <= EIG_LDS_DIM, by one wavefront; lds: its JAC_LDS doubles.
 constexpr int JAC_LDS = 3 * EIG_LDS_DIM * EIG_LDS_DIM + 5 * EIG_LDS_DIM;
 __device__ __forceinline__ void eigh_jacobi(int d, const double *in, double *wb, double *out, int32_t *info,
                                             double *lds) {
     constexpr int NP = EIG_LDS_DIM / 2;  // pairs per round
-    constexpr int NT = TRI_TPB;
     constexpr int NE = EIG_LDS_DIM * EIG_LDS_DIM;
+    constexpr int NT = 64;
+    static_assert(NT >= NE, "an element a lane");
     double *V = lds, *part = V + NE, *A = part + NE, *diag = A + NE + EIG_LDS_DIM;
     double *rc = diag + EIG_LDS_DIM, *rs = rc + NP;
     int *rp = (int *)(rs + NP), *rq = rp + NP, *rf = rq + NP;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x & 63;
     const int lda = d + 1;
     if (tid < NE) part[tid] = tid < d * d ? in[tid] * in[tid] : 0.0;
-    __syncthreads();
+    wave_sync_lds();
     if (tid == 0) {
         double s = 0.0;
         for (int i = 0; i < NE; ++i) s += part[i];
         part[0] = sqrt(s);
     }
-    __syncthreads();
+    wave_sync_lds();
     // rotations below this size are skipped: the off-diagonal part left is
     // at the rounding level of the matrix norm
     const double thr = part[0] * 0x1p-53 / d;
@@ -80,7 +87,7 @@ __device__ __forceinline__ void eigh_jacobi(int d, const double *in, double *wb,
         A[r * lda + c] = in[e];
         V[r * d + c] = (r == c) ? 1.0 : 0.0;
     }
-    __syncthreads();
+    wave_sync_lds();
     const int m = d + (d & 1) - 1;  // rounds per sweep; index m is a dummy when d is odd
     const int np = (m + 1) / 2;
     int sweep = 0;
@@ -114,7 +121,8 @@ __device__ __forceinline__ void eigh_jacobi(int d, const double *in, double *wb,
                 rf[k] = rot;
                 any |= rot;
             }
-            any = __syncthreads_or(any);
+            any = __builtin_amdgcn_ballot_w64(any) != 0;
+            wave_sync_lds();
             if (!any) continue;
             rotated = 1;
             // A_kl <- J_k^T A_kl J_l for every pair of pairs; the rotated
@@ -153,14 +161,14 @@ __device__ __forceinline__ void eigh_jacobi(int d, const double *in, double *wb,
                 V[i * d + pl] = cl * vp - sl * vq;
                 V[i * d + ql] = sl * vp + cl * vq;
             }
-            __syncthreads();
+            wave_sync_lds();
         }
         done = !rotated;
     }
     // eigenvalues in descending order (ties by index), eigenvectors with the
     // first entry of largest magnitude positive
     for (int i = tid; i < d; i += NT) diag[i] = A[i * lda + i];
-    __syncthreads();
+    wave_sync_lds();
     for (int i = tid; i < d; i += NT) {
         const double wi = diag[i];
         int rank = 0;
@@ -234,7 +242,17 @@ constexpr int HH_REG_DIM = HH_WAVES * 4 * 3;  // largest order reduced there: 12
 constexpr int HH_VEC = 64 * 3;                // LDS vectors of that reduction
 static_assert(HH_REG_DIM <= HH_VEC, "vectors as long as the order");
 static_assert(5 * HH_VEC <= EIG_MAX_DIM && TRI_WAVES * HH_VEC <= 2 * EIG_MAX_DIM, "its LDS in the pool of the larger orders");
-static_assert(JAC_LDS <= TRI_TPB, "the Jacobi method in the partial products' place");
+// Blocks of the Jacobi method per workgroup of k_eigh_hh, a wavefront each, in the
+// partial products' place: one while there are no more blocks than compute units
+// (a wavefront is faster alone: order 8, 40 us against 55 with four on a compute unit), then so many
+// that their workgroups, which hold a compute unit each, fit the chip at once.  Odd,
+// so that the first blocks of the groups fall on all XCDs and their quarters (workgroup
+// b's place follows b mod 32).  With one block a workgroup always, calls on 300 / 1000 /
+// 3000 blocks of order 8 took 193 / 274 / 718 us, here 131 / 138 / 222; with a kernel of
+// their own 119 / 131 / 205, but its launch adds 40 us where larger blocks are among them.
+constexpr int JAC_MAX = 13, CUS = 256;
+static_assert(JAC_MAX <= TRI_WAVES && JAC_MAX * JAC_LDS <= TRI_WAVES * HH_VEC, "room for the blocks");
+static int jacobi_per(int nblk) { return nblk <= CUS ? 1 : std::min((nblk + CUS - 1) / CUS | 1, JAC_MAX); }
 
 // ------------------------------------------------------------------ divide and conquer
 // The symmetric tridiagonal eigenproblem of orders up to DC_MAX by Cuppen's
@@ -277,12 +295,6 @@ __device__ __forceinline__ double group_prod(double v, int G) {
     case 32: return group_prod<32>(v);
     default: return group_prod<64>(v);
     }
-}
-
-// LDS writes of a wavefront's lanes are visible to its other lanes after it
-__device__ __forceinline__ void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
 }
 
 // 1/x: the hardware reciprocal refined by one Newton step
@@ -1113,7 +1125,7 @@ __device__ __forceinline__ void hh_reduce(int d, size_t D, const double *Z, doub
 __global__ __launch_bounds__(TRI_TPB) void k_eigh_hh(int nblk, const int64_t *__restrict__ off,
                                                      const int32_t *__restrict__ dim, const int64_t *__restrict__ woff,
                                                      const double *__restrict__ a, double *__restrict__ w,
-                                                     double *__restrict__ u, int32_t *__restrict__ info) {
+                                                     double *__restrict__ u, int32_t *__restrict__ info, int per) {
     __shared__ double2 P0[HH_VEC], P1[HH_VEC];  // (v, w) of two steps
     __shared__ double srow[HH_VEC];
     __shared__ double spart[TRI_WAVES * HH_VEC];
@@ -1125,12 +1137,18 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_hh(int nblk, const int64_t *__
         return;
     }
     if (d > HH_REG_DIM) return;  // reduced by k_eigh_tri
-    const double *Z = a + off[b];
-    double *A = u + off[b], *wb = w + woff[b];
     if (d <= EIG_LDS_DIM) {
-        eigh_jacobi(d, Z, wb, A, info ? info + b : nullptr, spart);
+        // the first such block of a group of per: all of the group's, a wavefront each
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g0 = b / per * per;
+        const int dl = lane < per && g0 + lane < nblk ? dim[g0 + lane] : 0;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(dl >= 1 && dl <= EIG_LDS_DIM);
+        if (g0 + __builtin_ctzll(mask) != b || !(mask >> wave & 1)) return;
+        const int bj = g0 + wave;
+        eigh_jacobi(dim[bj], a + off[bj], w + woff[bj], u + off[bj], info ? info + bj : nullptr, spart + wave * JAC_LDS);
         return;
     }
+    const double *Z = a + off[b];
+    double *A = u + off[b], *wb = w + woff[b];
     for (int j = threadIdx.x; j < HH_VEC; j += TRI_TPB) P0[j] = make_double2(0.0, 0.0);  // no update is pending
     if (d <= HH_WAVES * 4)
         hh_reduce<1>(d, d, Z, A, wb, P0, P1, srow, spart);
@@ -1839,13 +1857,17 @@ __global__ __launch_bounds__(BK_TPB) void k_eigh_back(int nblk, const int64_t *_
 
 constexpr int OUT_COLS = 32;  // columns of u per workgroup of k_eigh_out
 constexpr int OUT_TPB = 256;
+constexpr int OUT_FILL = 16384;
 
 // Output of the divide-and-conquer blocks: the columns of E (a, column-major)
 // into u (row-major), column c the one whose index k_eigh_tri left at u(c, c),
 // with its first entry of largest magnitude positive.  Workgroup (b, p) owns
-// columns [32 p, 32 p + 32) of u, 32 x 32 tiles through LDS, read down the
+// columns [32 p, 32 p + 32) of u (and those a grid of panels further), 32 x 32 tiles through LDS, read down the
 // columns of E and written along the rows of u: 13 us at order 180, a chain of
-// three reads (48 us with one workgroup per block and a staging copy).
+// three reads (48 us with one workgroup per block and a staging copy).  Most
+// workgroups find no columns where blocks are small, and a thousand blocks fill the
+// chip with one panel each: OUT_FILL of them at most.  (10000 blocks of order 1, which
+// have none: 327 us a call with all 16 panels, 286.)
 __global__ __launch_bounds__(OUT_TPB) void k_eigh_out(int nblk, const int64_t *__restrict__ off,
                                                       const int32_t *__restrict__ dim, const double *__restrict__ a,
                                                       double *__restrict__ u) {
@@ -1858,65 +1880,66 @@ __global__ __launch_bounds__(OUT_TPB) void k_eigh_out(int nblk, const int64_t *_
     if (b >= nblk) return;
     const int d = dim[b];
     if (d <= EIG_LDS_DIM || d > DC_MAX) return;
-    const int c0 = blockIdx.y * OUT_COLS;
-    if (c0 >= d) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const size_t D = (size_t)d;
     const double *E = a + off[b];
     double *U = u + off[b];
-    if (tid < OUT_COLS) {
-        const int c = min(c0 + tid, d - 1);
-        src[tid] = min(max((int)U[c * D + c], 0), d - 1);
-    }
-    __syncthreads();
-    double best[NC];
-    int bi[NC];  // twice the row, and the sign
+    for (int c0 = blockIdx.y * OUT_COLS; c0 < d; c0 += gridDim.y * OUT_COLS) {
+        if (tid < OUT_COLS) {
+            const int c = min(c0 + tid, d - 1);
+            src[tid] = min(max((int)U[c * D + c], 0), d - 1);
+        }
+        __syncthreads();
+        double best[NC];
+        int bi[NC];  // twice the row, and the sign
 #pragma unroll
-    for (int e = 0; e < NC; ++e) {
-        best[e] = -1.0;
-        bi[e] = 0;
-    }
-    for (int r = lane; r < d; r += 64) {
-        double av[NC];
+        for (int e = 0; e < NC; ++e) {
+            best[e] = -1.0;
+            bi[e] = 0;
+        }
+        for (int r = lane; r < d; r += 64) {
+            double av[NC];
 #pragma unroll
-        for (int e = 0; e < NC; ++e) av[e] = E[src[NC * wv + e] * D + r];
+            for (int e = 0; e < NC; ++e) av[e] = E[src[NC * wv + e] * D + r];
 #pragma unroll
-        for (int e = 0; e < NC; ++e)
-            if (fabs(av[e]) > best[e]) {
-                best[e] = fabs(av[e]);
-                bi[e] = 2 * r + (av[e] < 0.0);
+            for (int e = 0; e < NC; ++e)
+                if (fabs(av[e]) > best[e]) {
+                    best[e] = fabs(av[e]);
+                    bi[e] = 2 * r + (av[e] < 0.0);
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < NC; ++e) {
+            for (int o = 32; o > 0; o >>= 1) {
+                const double ob = __shfl_xor(best[e], o, 64);
+                const int oi = __shfl_xor(bi[e], o, 64);
+                if (ob > best[e] || (ob == best[e] && oi < bi[e])) {
+                    best[e] = ob;
+                    bi[e] = oi;
+                }
             }
-    }
+            if (lane == 0) ssg[NC * wv + e] = (bi[e] & 1) ? -1.0 : 1.0;
+        }
+        __syncthreads();
+        const int tr = tid & 31, tc = tid >> 5;
+        double x[32 / NR];
+        auto fetch = [&](int rr) {
 #pragma unroll
-    for (int e = 0; e < NC; ++e) {
-        for (int o = 32; o > 0; o >>= 1) {
-            const double ob = __shfl_xor(best[e], o, 64);
-            const int oi = __shfl_xor(bi[e], o, 64);
-            if (ob > best[e] || (ob == best[e] && oi < bi[e])) {
-                best[e] = ob;
-                bi[e] = oi;
+            for (int q = 0; q < 32 / NR; ++q) x[q] = E[src[tc + NR * q] * D + min(rr + tr, d - 1)];
+        };
+        fetch(0);
+        for (int rr = 0, h = 0; rr < d; rr += 32, h ^= 1) {
+#pragma unroll
+            for (int q = 0; q < 32 / NR; ++q) tile[h][tc + NR * q][tr] = ssg[tc + NR * q] * x[q];
+            __syncthreads();  // (the other buffer is read up to here: two are enough)
+            if (rr + 32 < d) fetch(rr + 32);
+#pragma unroll
+            for (int q = 0; q < 32 / NR; ++q) {
+                const int r = rr + tc + NR * q, c = c0 + tr;
+                if (r < d && c < d) U[r * D + c] = tile[h][tr][tc + NR * q];
             }
         }
-        if (lane == 0) ssg[NC * wv + e] = (bi[e] & 1) ? -1.0 : 1.0;
-    }
-    __syncthreads();
-    const int tr = tid & 31, tc = tid >> 5;
-    double x[32 / NR];
-    auto fetch = [&](int rr) {
-#pragma unroll
-        for (int q = 0; q < 32 / NR; ++q) x[q] = E[src[tc + NR * q] * D + min(rr + tr, d - 1)];
-    };
-    fetch(0);
-    for (int rr = 0, h = 0; rr < d; rr += 32, h ^= 1) {
-#pragma unroll
-        for (int q = 0; q < 32 / NR; ++q) tile[h][tc + NR * q][tr] = ssg[tc + NR * q] * x[q];
-        __syncthreads();  // (the other buffer is read up to here: two are enough)
-        if (rr + 32 < d) fetch(rr + 32);
-#pragma unroll
-        for (int q = 0; q < 32 / NR; ++q) {
-            const int r = rr + tc + NR * q, c = c0 + tr;
-            if (r < d && c < d) U[r * D + c] = tile[h][tr][tc + NR * q];
-        }
+        __syncthreads();  // src, ssg and tile are the next columns'
     }
 }
 
@@ -2058,10 +2081,12 @@ dmrg_status dmrg_eigh_blocks(int32_t nblk, const int64_t *off, const int32_t *di
     if (!off || !dim || !woff || !a || !w || !u) return set_error(DMRG_E_INVALID_ARG, "null argument");
     if (a == u || a == w || u == w) return set_error(DMRG_E_INVALID_ARG, "a, w and u must not overlap");
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_eigh_hh, dim3(nblk), dim3(TRI_TPB), 0, s, nblk, off, dim, woff, (const double *)a, w, u, info);
+    hipLaunchKernelGGL(k_eigh_hh, dim3(nblk), dim3(TRI_TPB), 0, s, nblk, off, dim, woff, (const double *)a, w, u, info,
+                       jacobi_per(nblk));
     hipLaunchKernelGGL(k_eigh_tri, dim3(nblk), dim3(TRI_TPB), 0, s, nblk, off, dim, woff, a, w, u, info);
     hipLaunchKernelGGL(k_eigh_back, dim3(nblk, BK_PANELS), dim3(BK_TPB), 0, s, nblk, off, dim, a, (const double *)u);
-    hipLaunchKernelGGL(k_eigh_out, dim3(nblk, DC_MAX / OUT_COLS), dim3(OUT_TPB), 0, s, nblk, off, dim, (const double *)a, u);
+    const int panels = std::min(DC_MAX / OUT_COLS, std::max(1, OUT_FILL / nblk));
+    hipLaunchKernelGGL(k_eigh_out, dim3(nblk, panels), dim3(OUT_TPB), 0, s, nblk, off, dim, (const double *)a, u);
     DMRG_HIP(hipGetLastError());
     return DMRG_OK;
 }
