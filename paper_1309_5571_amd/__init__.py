@@ -678,15 +678,14 @@ _RENORM_BLOCK = struct.Struct("4q5i4x")  # the layout of N.RenormBlock
 def _renorm_blocks(blocks):
     """The blocks of renormalize as an array of N.RenormBlock, packed at once (60
     blocks: 60 us; a ctypes structure each: 160 us, more than the GPU's work)."""
+    n = len(blocks)
+    rows = [tuple(map(int, b)) for b in blocks]  # (a block's fields may be an iterator)
     try:
         pack = _RENORM_BLOCK.pack
-        data = b"".join([pack(*map(int, b)) for b in blocks])
-        return (N.RenormBlock * max(len(blocks), 1)).from_buffer_copy(data or bytes(_RENORM_BLOCK.size))
+        data = b"".join([pack(*r) for r in rows])
+        return (N.RenormBlock * max(n, 1)).from_buffer_copy(data or bytes(_RENORM_BLOCK.size))
     except struct.error:  # fields left out, or past the range of their type
-        arr = (N.RenormBlock * len(blocks))()
-        for i, b in enumerate(blocks):
-            arr[i] = N.RenormBlock(*[int(x) for x in b])
-        return arr
+        return (N.RenormBlock * n)(*[N.RenormBlock(*r) for r in rows])
 
 
 def renormalize(data, u, blocks, out_len: int):

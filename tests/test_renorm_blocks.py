@@ -19,3 +19,16 @@ def test_packed_blocks(blocks):
     for i, b in enumerate(blocks):
         ref[i] = N.RenormBlock(*[int(v) for v in b])
     assert bytes(dm._renorm_blocks(blocks)) == bytes(ref)
+
+
+@pytest.mark.parametrize("block", [(1, 2, 3, 4, 5, 6, 7, 8, 1), (1, 2, 3, 4, 5, 6, 7, 8),
+                                   (1, 2, 3, 4, 2 ** 32 + 5, 6, 7, 8, 0)], ids=["whole", "short", "wide"])
+def test_fields_from_an_iterator(block):
+    """A block's fields may come from an iterator, read once whichever way it is packed."""
+    ref = (N.RenormBlock * 1)(N.RenormBlock(*block))
+    assert bytes(dm._renorm_blocks([iter(block)])) == bytes(ref)
+
+
+def test_generator_of_blocks_is_refused():
+    with pytest.raises(TypeError):
+        dm.renormalize(None, None, (b for b in [(1, 2, 3, 4, 5, 6, 7, 8, 1)]), 1)
