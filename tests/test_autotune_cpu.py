@@ -34,3 +34,19 @@ def test_stored_table_is_valid():
     for key, ent in tab["entries"].items():
         assert set(ent["tiles"]) <= {16, 32}, key
         assert list(ent["bounds"]) == sorted(ent["bounds"]), key
+
+
+def test_stored_tables_are_candidates():
+    """A new run of the tuner can come to every stored entry."""
+    tab = json.load(open(autotune.TABLE_PATH))
+    for key, ent in tab["entries"].items():
+        assert (tuple(ent["bounds"]), tuple(ent["tiles"])) in autotune.CANDIDATES, key
+
+
+def test_pick_counts_both_precisions_and_keeps_the_stored_table():
+    rows = [{"bounds": [b], "tiles": [16], "us": u, "us_f64": f} for b, u, f in
+            [(1, 31.0, 33.0), (2, 32.5, 25.0), (3, 32.7, 25.1)]]
+    assert autotune.pick(rows, "f32", None)["bounds"] == [2]
+    assert autotune.pick(rows, "f32", ((3,), (16,)))["bounds"] == [3]  # as fast
+    assert autotune.pick(rows, "f32", ((1,), (16,)))["bounds"] == [2]  # its FP64 passes are slower
+    assert autotune.pick(rows, "f64", None)["bounds"] == [1]
