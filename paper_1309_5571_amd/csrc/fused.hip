@@ -236,7 +236,7 @@ __device__ __forceinline__ void diag_ahead(double (&v)[2], uint32_t dw, int n, c
 // descriptors, 0 if not packed.  ADJ: a tile of the adjoint; with GRAD also the
 // coefficient gradient's share <xg, segment product> of every segment and diagonal
 // term (out, and with it coef, may be null then).  Hubbard m = 2048, calls back to
-// back, us for the adjoint / the gradient / both in one pass: 8.2 / 14.3 / 14.9 against
+// back, us for the adjoint / the gradient / both in one pass: 8.9 / 14.4 / 15.0 against
 // 25.2 / 29.2 / 32.1 on 32 x 32 tiles (two launches; contractions below 16 value by
 // value) and 19.8 / 23.1 / 43.1 on the task kernel.
 template <int PREC, bool ADJ, bool GRAD>

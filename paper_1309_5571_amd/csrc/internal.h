@@ -144,14 +144,14 @@ struct Record {
     double w;
 };
 
-// One run of a wide tile's contraction: its segments' items of 16 (a copy
-// segment is one item) in list order, cut into TWA (intermediates) or TWB
-// (outputs) runs whose lengths differ by at most one.
+// One run of a wide output tile's contraction: its segments' items of 16 (a copy
+// segment is one item) in list order, cut into TWB runs whose lengths differ by at
+// most one.  (An intermediate has one segment, and its TWA runs need no list.)
 constexpr int TWA = 4, TWB = 8;
 struct Split {
     int32_t seg, kb;  // first segment with an item of the run, and that item's index in it
     int32_t n;        // items of the run
-    int32_t part;     // adjoint output tiles: the run's first coefficient-gradient slot (one per segment it meets)
+    int32_t part;     // adjoint: the run's first coefficient-gradient slot (one per segment it meets)
 };
 
 struct Lists {  // device task lists of one pass
@@ -159,7 +159,7 @@ struct Lists {  // device task lists of one pass
     int32_t ntask = 0;
     int32_t ns = 1;  // 16 x 16 sub-tiles per tile side: 1 when every tile fits 16 x 16, else 2
     int32_t stride = 0, dstride = 0;  // descriptors of consecutive tiles' segments / diagonal terms, 0: not packed
-    Split *splits = nullptr;  // passes of 32-wide tiles: [ntask * TWA] (stage A) or [ntask * TWB]
+    Split *splits = nullptr;  // output tiles of 32-wide passes: [ntask * TWB]
 };
 
 struct PassSet {  // everything one projection direction needs in one precision

@@ -246,7 +246,7 @@ static dmrg_status analyse(const dmrg_problem *p, MemberPairs *mp_out, std::vect
 
 struct HostPass {
     std::vector<Task> A, B;
-    std::vector<Split> splitA, splitB;  // wide passes
+    std::vector<Split> splitB;          // wide passes
     int wide = 0;                       // see PassSet
     bool small = true;
     std::vector<Seg> segs;
@@ -273,7 +273,7 @@ constexpr double WIDE64_MIN = 200.0;
 
 // Adjoint passes take 16 x 16 tiles where the forward pass does and no block is above
 // this order.  Adjoint / gradient / both, us on 16 x 16 against 32 x 32 tiles: Hubbard
-// m = 2048 (order 36) 8 / 14 / 15 against 25 / 29 / 32, Heisenberg m = 512 (90) 15 / 17 / 18
+// m = 2048 (order 36) 9 / 14 / 15 against 25 / 29 / 32, Heisenberg m = 512 (90) 15 / 17 / 18
 // against 17 / 24 / 25, Hubbard m = 5120 (90) 57 / 75 / 79 against 59 / 71 / 77, m = 6144
 // (108) 82 / 104 / 110 against 71 / 88 / 96, Heisenberg m = 1024 (180) 31 / 38 / 39
 // against 24 / 33 / 34.
@@ -408,15 +408,15 @@ static void pack_tiles(HostPass &hp, int32_t *stride, int32_t *dstride) {
     *dstride = nd;
 }
 
-// The TW runs of every tile of a wide stage, in task order.  With slots, the
+// The TWB runs of every output tile of a wide pass, in task order.  With per_term, the
 // coefficient-gradient partials are numbered too: one per run and segment,
 // then one per diagonal term of the tile (Task::part0), listed per term.
-static void make_splits(int TW, std::vector<Task> &tasks, const std::vector<Seg> &segs, std::vector<Split> &out,
-                        const std::vector<DiagTerm> *diags, std::vector<std::vector<int32_t>> *per_term,
-                        int32_t *npart) {
+static void make_splits(HostPass &hp, std::vector<std::vector<int32_t>> *per_term, int32_t *npart) {
+    constexpr int TW = TWB;
+    const std::vector<Seg> &segs = hp.segs;
     int32_t part = 0;
-    out.reserve(out.size() + tasks.size() * TW);
-    for (Task &t : tasks) {
+    hp.splitB.reserve(hp.B.size() * TW);
+    for (Task &t : hp.B) {
         const int64_t total = t.nitem;
         int s = t.seg_begin, kb = 0;
         for (int w = 0; w < TW; ++w) {
@@ -440,12 +440,12 @@ static void make_splits(int TW, std::vector<Task> &tasks, const std::vector<Seg>
                 kb += take;
                 n -= take;
             }
-            out.push_back(sp);
+            hp.splitB.push_back(sp);
         }
         t.part0 = part;
         if (per_term)
             for (int d = t.diag_begin; d < t.diag_end; ++d, ++part)
-                if ((*diags)[d].term >= 0) (*per_term)[(*diags)[d].term].push_back(part);
+                if (hp.diags[d].term >= 0) (*per_term)[hp.diags[d].term].push_back(part);
     }
     if (npart) *npart = part;
 }
@@ -455,7 +455,7 @@ static void make_splits(int TW, std::vector<Task> &tasks, const std::vector<Seg>
 // diagonal term.
 static void gradient_slots(HostPass &hp, std::vector<std::vector<int32_t>> &per_term, int32_t *npart) {
     if (hp.wide) {
-        make_splits(TWB, hp.B, hp.segs, hp.splitB, &hp.diags, &per_term, npart);
+        make_splits(hp, &per_term, npart);
         return;
     }
     int32_t part = 0;
@@ -807,6 +807,44 @@ static dmrg_status upload(dmrg_plan *plan, const std::vector<T> &v, T **dst, hip
     return DMRG_OK;
 }
 
+// The lists of a pass in one allocation, and in one copy where they are short: an
+// allocation and a copy take some 10 us each, a good part of a small plan's creation.
+struct ListUpload {
+    static constexpr size_t PACK_MAX = 256 * 1024;
+    struct Piece {
+        const void *src;
+        size_t bytes;
+        void **dst;
+    };
+    std::vector<Piece> pieces;
+    template <class T>
+    void add(const std::vector<T> &v, T **dst) {
+        *dst = nullptr;
+        if (!v.empty()) pieces.push_back(Piece{v.data(), v.size() * sizeof(T), (void **)dst});
+    }
+    dmrg_status commit(dmrg_plan *plan, hipStream_t s) {
+        auto padded = [](size_t n) { return (n + 255) & ~(size_t)255; };
+        size_t total = 0;
+        for (const Piece &p : pieces) total += padded(p.bytes);
+        if (!total) return DMRG_OK;
+        char *dev = nullptr;
+        DMRG_HIP(hipMalloc((void **)&dev, total));
+        plan->owned.push_back(dev);
+        std::vector<char> host(total <= PACK_MAX ? total : 0);
+        size_t at = 0;
+        for (const Piece &p : pieces) {
+            if (host.empty())
+                DMRG_HIP(hipMemcpyAsync(dev + at, p.src, p.bytes, hipMemcpyHostToDevice, s));
+            else
+                memcpy(host.data() + at, p.src, p.bytes);
+            *p.dst = dev + at;
+            at += padded(p.bytes);
+        }
+        if (!host.empty()) DMRG_HIP(hipMemcpyAsync(dev, host.data(), total, hipMemcpyHostToDevice, s));
+        return DMRG_OK;
+    }
+};
+
 static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, bool low, bool pack, hipStream_t s) {
     if (pack) pack_tiles(hp, &ps.stageB.stride, &ps.stageB.dstride);
     // member-contiguous rows for the per-tile Rayleigh partials of stage B
@@ -815,11 +853,14 @@ static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, bool 
     for (int m = 0; m < plan->nprob; ++m) begin[m + 1] += begin[m];
     next.assign(begin.begin(), begin.end() - 1);
     for (Task &t : hp.B) t.rslot = next[t.member]++;
-    DMRG_TRY(upload(plan, begin, &ps.slot_begin, s));
-    DMRG_TRY(upload(plan, hp.segs, &ps.segs, s));
-    DMRG_TRY(upload(plan, hp.diags, &ps.diags, s));
-    DMRG_TRY(upload(plan, hp.A, &ps.stageA.tasks, s));
-    DMRG_TRY(upload(plan, hp.B, &ps.stageB.tasks, s));
+    ListUpload lists;
+    lists.add(begin, &ps.slot_begin);
+    lists.add(hp.segs, &ps.segs);
+    lists.add(hp.diags, &ps.diags);
+    lists.add(hp.A, &ps.stageA.tasks);
+    lists.add(hp.B, &ps.stageB.tasks);
+    lists.add(hp.splitB, &ps.stageB.splits);
+    DMRG_TRY(lists.commit(plan, s));
     ps.stageA.ntask = (int32_t)hp.A.size();
     ps.stageB.ntask = (int32_t)hp.B.size();
     for (const Task &t : hp.A)
@@ -830,8 +871,6 @@ static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, bool 
         return set_error(DMRG_E_INVALID_ARG, "internal: a tile above 16 in a pass of 16 x 16 tiles");
     ps.wide = hp.wide;
     ps.small = hp.small;
-    DMRG_TRY(upload(plan, hp.splitA, &ps.stageA.splits, s));
-    DMRG_TRY(upload(plan, hp.splitB, &ps.stageB.splits, s));
     ps.nseg = (int32_t)hp.segs.size();
     ps.ndiag = (int32_t)hp.diags.size();
     ps.tmp_elems = hp.tmp;
@@ -1018,11 +1057,7 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
     HostPass f64, a64;
     build_pass(plan, false, nullptr, 0, f64);
     build_pass(plan, true, nullptr, 0, a64);
-    if (f64.wide == 32) {
-        make_splits(TWA, f64.A, f64.segs, f64.splitA, nullptr, nullptr, nullptr);
-        make_splits(TWB, f64.B, f64.segs, f64.splitB, nullptr, nullptr, nullptr);
-    }
-    if (a64.wide) make_splits(TWA, a64.A, a64.segs, a64.splitA, nullptr, nullptr, nullptr);
+    if (f64.wide == 32) make_splits(f64, nullptr, nullptr);
     // coefficient-gradient partial slots (adjoint stage B)
     {
         int32_t part = 0;
@@ -1047,7 +1082,8 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
         }
     }
     DMRG_TRY(upload_pass(plan, f64, plan->fwd[0], false, true, stream));
-    DMRG_TRY(upload_pass(plan, a64, plan->adj[0], false, true, stream));
+    // (not packed: 60 us of this plan's creation for 0.6 us of an adjoint, Hubbard m = 2048)
+    DMRG_TRY(upload_pass(plan, a64, plan->adj[0], false, false, stream));
     int64_t tmp = std::max(f64.tmp, a64.tmp);
 
     // ---- low-precision forward pass with converted operator copies

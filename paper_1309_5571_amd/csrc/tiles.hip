@@ -382,7 +382,13 @@ __global__ __launch_bounds__(64 * waves_of<MODE>()) __attribute__((amdgpu_waves_
     const int i16 = lane & 15, g = lane >> 4;
     const Task tk = tasks[blockIdx.x];
     if (mask && !mask[tk.member]) return;
-    const Split sp = splits[(int64_t)blockIdx.x * TW + wave];
+    Split sp;
+    if (MODE == 0) {
+        const int b = tk.nitem * wave / TW;
+        sp = Split{tk.seg_begin, b, tk.nitem * (wave + 1) / TW - b, 0};
+    } else {
+        sp = splits[(int64_t)blockIdx.x * TW + wave];
+    }
     const int cnt = tk.m * tk.n;
     constexpr int NQ = 1024 / (64 * TW);  // tile elements per thread
     DiagTerm dt0{};
