@@ -7,9 +7,12 @@
 //   stage B: every output tile of y, summing all of its records' second
 //            products, the one-sided records, and the diagonal terms, and
 //            writing the tile exactly once (no atomics, fixed order).
-// Both launches run the same grouped-GEMM kernel: one wavefront owns one
-// output tile of up to 32 x 32 (2 x 2 MFMA sub-tiles of 16 x 16) and walks
-// its list of GEMM segments.  The paper issues two cuBLAS dgemm calls per
+// The FP64 passes of wide tiles run on tiles.hip, the output tiles of 16 x 16
+// passes (FP64 and FP32) on fused.hip.  Here are the task kernel, for the
+// intermediates of 16 x 16 passes and for the other passes of reduced precision, and
+// the kernel of four vectors at a time: four wavefronts share an output tile of
+// up to 32 x 32 (2 x 2 MFMA sub-tiles of 16 x 16) and the work items of its
+// list of GEMM segments.  The paper issues two cuBLAS dgemm calls per
 // record on four CUDA streams (Alg. 6-7) to overlap many small GEMMs; here
 // every tile of every record is one entry of a single launch instead.
 //
@@ -23,6 +26,7 @@
 // Across segments, and in the diagonal epilogue, sums are FP64.
 #include <algorithm>
 #include <cstdio>
+#include <type_traits>
 
 #include "internal.h"
 #include "lanes.h"
@@ -131,39 +135,26 @@ struct Tr<DMRG_BF16> {
 
 // ------------------------------------------------------------------ operand fetch
 
-// P fragment: rows row (tile-local r), k = k0 + kstep j (k0: the lane's kbase)
-template <int PREC, bool PIN, bool PT, bool ST = false>
-__device__ __forceinline__ void load_p(typename Tr<PREC>::val_t (&v)[Tr<PREC>::KPL], const Seg &s,
-                                       const double *__restrict__ in, const void *__restrict__ tmp, int row,
-                                       bool row_ok, int k0, int K, double scale) {
+// Fragment of a fused segment's A block: row row, k = k0 + kstep j (k0: the lane's kbase)
+template <int PREC>
+__device__ __forceinline__ void load_a(typename Tr<PREC>::val_t (&v)[Tr<PREC>::KPL], const Seg &s, int row, bool row_ok,
+                                       int k0) {
     typedef Tr<PREC> T;
-    if (PIN) {
-        const gptr P = (gptr)in + s.p;
+    typedef gptr_of<typename T::store_t> S;
+    const S P = (S)(uintptr_t)s.p;
 #pragma unroll
-        for (int j = 0; j < T::KPL; ++j) {
-            int k = k0 + j * T::template kstep<ST>();
-            double x = 0.0;
-            if (row_ok && k < K) x = PT ? P[(int64_t)k * s.ldp + row] : P[(int64_t)row * s.ldp + k];
-            v[j] = T::from_in(x * scale);
-        }
-    } else {
-        typedef gptr_of<typename T::store_t> S;
-        const S P = (s.pkind == OPD_ABS) ? (S)(uintptr_t)s.p : (S)tmp + s.p;
-#pragma unroll
-        for (int j = 0; j < T::KPL; ++j) {
-            int k = k0 + j * T::template kstep<ST>();
-            typename T::store_t x = 0;
-            if (row_ok && k < K) x = PT ? P[(int64_t)k * s.ldp + row] : P[(int64_t)row * s.ldp + k];
-            v[j] = T::from_store(x);
-        }
+    for (int j = 0; j < T::KPL; ++j) {
+        const int k = k0 + j * T::template kstep<true>();
+        typename T::store_t x = 0;
+        if (row_ok && k < s.K) x = P[(int64_t)row * s.ldp + k];
+        v[j] = T::from_store(x);
     }
 }
 
 // Raw fragments for the reduced-precision paths: FP64 from the input vector,
 // the stored type from operator blocks and intermediates, converted to the
 // MFMA type only where consumed.  A conversion next to a guarded load makes the
-// wavefront wait for that load before it issues the next one (the FP64 path
-// needs no conversion and loads through load_p / load_q).
+// wavefront wait for that load before it issues the next one.
 template <int PREC, bool IN>
 struct RawT {
     typedef typename Tr<PREC>::store_t type;
@@ -359,7 +350,7 @@ __device__ __forceinline__ void fused_item(typename Tr<PREC>::acc_t (&acc)[2][2]
         const int kk = T::template kbase<true>(k0, g);
         if constexpr (T::KPL == 4) {  // FP32: raw FP64 input, converted at the MFMA
             double qr[4][T::KPL];
-            load_p<PREC, false, false, true>(pv, s, in, nullptr, prow, pok, kk, s.K, 1.0);
+            load_a<PREC>(pv, s, prow, pok, kk);
 #pragma unroll
             for (int cs = 0; cs < 4; ++cs) {
                 const int col = cs * 16 + r16;
@@ -371,7 +362,7 @@ __device__ __forceinline__ void fused_item(typename Tr<PREC>::acc_t (&acc)[2][2]
             for (int cs = 0; cs < 4; ++cs)
                 if (cs < ncs) cvt_frag<PREC, true>(qv[cs], qr[cs], 1.0);
         } else {  // BF16: unconditional loads, one sub-tile at a time
-            load_p<PREC, false, false, true>(pv, s, in, nullptr, prow, pok, kk, s.K, 1.0);
+            load_a<PREC>(pv, s, prow, pok, kk);
 #pragma unroll
             for (int cs = 0; cs < 4; ++cs) {
                 const int col = cs * 16 + r16;
@@ -445,30 +436,32 @@ __device__ __forceinline__ void seg_items(typename Tr<PREC>::acc_t (&acc)[2][2],
         item_gemm<PREC, NS, PIN, PT, QIN, QT>(acc, s, tk, in, tmp, nsr, nsc, it * kc_of<PREC>());
 }
 
-// One switch per segment on the operand layout (the task lists use 7 of the 16).
+// One switch per segment on the operand layout.
 template <int PREC, int NS>
 __device__ __forceinline__ void seg_dispatch(typename Tr<PREC>::acc_t (&acc)[2][2], const Seg &s, const Task &tk,
                                              const double *__restrict__ in, const void *__restrict__ tmp, int nsr,
                                              int nsc, int first, int nit) {
     const bool pin = s.pkind == OPD_IN, qin = s.qkind == OPD_IN;
     const int code = (pin ? 8 : 0) | (s.ptrans ? 4 : 0) | (qin ? 2 : 0) | (s.qtrans ? 1 : 0);
-    switch (code) {
-        case 0: seg_items<PREC, NS, false, false, false, false>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 1: seg_items<PREC, NS, false, false, false, true>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 2: seg_items<PREC, NS, false, false, true, false>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 3: seg_items<PREC, NS, false, false, true, true>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 4: seg_items<PREC, NS, false, true, false, false>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 5: seg_items<PREC, NS, false, true, false, true>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 6: seg_items<PREC, NS, false, true, true, false>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 7: seg_items<PREC, NS, false, true, true, true>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 8: seg_items<PREC, NS, true, false, false, false>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 9: seg_items<PREC, NS, true, false, false, true>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 10: seg_items<PREC, NS, true, false, true, false>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 11: seg_items<PREC, NS, true, false, true, true>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 12: seg_items<PREC, NS, true, true, false, false>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 13: seg_items<PREC, NS, true, true, false, true>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        case 14: seg_items<PREC, NS, true, true, true, false>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
-        default: seg_items<PREC, NS, true, true, true, true>(acc, s, tk, in, tmp, nsr, nsc, first, nit); break;
+    auto go = [&](auto p_in, auto p_t, auto q_in, auto q_t) {
+        seg_items<PREC, NS, p_in.value, p_t.value, q_in.value, q_t.value>(acc, s, tk, in, tmp, nsr, nsc, first, nit);
+    };
+    const std::true_type y;
+    const std::false_type n;
+    if (code == 2)
+        go(n, n, y, n);  // A X
+    else if (code == 9)
+        go(y, n, n, y);  // X B^T
+    else if constexpr (PREC == DMRG_F64) {  // (intermediates only; these two of the adjoint)
+        if (code == 6)
+            go(n, y, y, n);  // A^T X
+        else
+            go(y, n, n, n);  // X B
+    } else {
+        if (code == 1)
+            go(n, n, n, y);  // T B^T
+        else
+            go(n, n, n, n);  // A T
     }
 }
 
@@ -558,13 +551,13 @@ __device__ __forceinline__ void tasks_run(const Task *__restrict__ tasks, int nt
         int q = 0;  // work-item counter, identical in every wavefront
         for (int si = tk.seg_begin; si < tk.seg_end; ++si) {
             const int K = segs[si].K;
-            const bool fused = segs[si].fused != 0;
+            const bool fused = MODE == 1 && segs[si].fused != 0;  // (an intermediate's segment is a product)
             const int nit = fused ? 1 : (K + kc_of<PREC>() - 1) / kc_of<PREC>();  // a fused segment is one item
             const int first = (wave - q % PW + PW) % PW;  // first item of this segment owned by this wave
             if (first < nit) {
                 const Seg s = segs[si];
                 const double c = (s.coef >= 0 ? coef[s.coef] : 1.0) * s.w;
-                if (s.fused == 2) {  // copy segment, summed in FP64
+                if (MODE == 1 && s.fused == 2) {  // copy segment, summed in FP64
                     double cv[NS][NS][4];
                     copy_item<PREC, NS>(cv, s, tk, in);
 #pragma unroll
@@ -749,7 +742,7 @@ __device__ __forceinline__ void fused_item_nv(v4d (&acc)[NV], const Seg &s, cons
 // One work item of a non-fused segment for NVEC vectors: the operand that is
 // the call's input or the intermediate differs per vector (offset v stride),
 // the operator block is loaded once.
-template <bool PIN, bool PT, bool QIN, bool QT>
+template <bool PIN, bool QIN, bool QT>
 __device__ __forceinline__ void item_gemm_nv(v4d (&acc)[NVEC], const Seg &s, const Task &tk,
                                              const double *__restrict__ in, const double *__restrict__ tmp,
                                              const MultiArgs &ma, int k0) {
@@ -775,9 +768,9 @@ __device__ __forceinline__ void item_gemm_nv(v4d (&acc)[NVEC], const Seg &s, con
             load_raw<DMRG_F64, QIN, !QT, false>(sh[b], Q, s.ldq, qcol, qok, kk, s.K);
 #pragma unroll
             for (int v = 0; v < NVEC; ++v)
-                load_raw<DMRG_F64, PIN, PT, false>(pvec[v][b], P + v * pstr, s.ldp, prow, pok, kk, s.K);
+                load_raw<DMRG_F64, PIN, false, false>(pvec[v][b], P + v * pstr, s.ldp, prow, pok, kk, s.K);
         } else {
-            load_raw<DMRG_F64, PIN, PT, false>(sh[b], P, s.ldp, prow, pok, kk, s.K);
+            load_raw<DMRG_F64, PIN, false, false>(sh[b], P, s.ldp, prow, pok, kk, s.K);
 #pragma unroll
             for (int v = 0; v < NVEC; ++v)
                 load_raw<DMRG_F64, QIN, !QT, false>(pvec[v][b], Q + v * qstr, s.ldq, qcol, qok, kk, s.K);
@@ -799,20 +792,14 @@ __device__ __forceinline__ void seg_items_nv(v4d (&acc)[NVEC], const Seg &s, con
                                              const double *__restrict__ in, const double *__restrict__ tmp,
                                              const MultiArgs &ma, int first, int nit) {
     const bool pin = s.pkind == OPD_IN, qin = s.qkind == OPD_IN;
-    const int code = (pin ? 8 : 0) | (s.ptrans ? 4 : 0) | (qin ? 2 : 0) | (s.qtrans ? 1 : 0);
+    const int code = (pin ? 4 : 0) | (qin ? 2 : 0) | (s.qtrans ? 1 : 0);
     for (int it = first; it < nit; it += PW) {
         const int k0 = it * NV_KC;
         switch (code) {
-            case 0: item_gemm_nv<false, false, false, false>(acc, s, tk, in, tmp, ma, k0); break;
-            case 1: item_gemm_nv<false, false, false, true>(acc, s, tk, in, tmp, ma, k0); break;
-            case 2: item_gemm_nv<false, false, true, false>(acc, s, tk, in, tmp, ma, k0); break;
-            case 3: item_gemm_nv<false, false, true, true>(acc, s, tk, in, tmp, ma, k0); break;
-            case 4: item_gemm_nv<false, true, false, false>(acc, s, tk, in, tmp, ma, k0); break;
-            case 5: item_gemm_nv<false, true, false, true>(acc, s, tk, in, tmp, ma, k0); break;
-            case 8: item_gemm_nv<true, false, false, false>(acc, s, tk, in, tmp, ma, k0); break;
-            case 9: item_gemm_nv<true, false, false, true>(acc, s, tk, in, tmp, ma, k0); break;
-            case 12: item_gemm_nv<true, true, false, false>(acc, s, tk, in, tmp, ma, k0); break;
-            default: item_gemm_nv<true, true, false, true>(acc, s, tk, in, tmp, ma, k0); break;
+            case 2: item_gemm_nv<false, true, false>(acc, s, tk, in, tmp, ma, k0); break;   // A X
+            case 5: item_gemm_nv<true, false, true>(acc, s, tk, in, tmp, ma, k0); break;    // X B^T
+            case 1: item_gemm_nv<false, false, true>(acc, s, tk, in, tmp, ma, k0); break;   // T B^T
+            default: item_gemm_nv<false, false, false>(acc, s, tk, in, tmp, ma, k0); break; // A T
         }
     }
 }
