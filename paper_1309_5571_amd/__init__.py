@@ -679,13 +679,13 @@ def _renorm_blocks(blocks):
     """The blocks of renormalize as an array of N.RenormBlock, packed at once (60
     blocks: 60 us; a ctypes structure each: 160 us, more than the GPU's work)."""
     n = len(blocks)
-    rows = [tuple(map(int, b)) for b in blocks]  # (a block's fields may be an iterator)
+    rows = list(map(tuple, blocks))  # (a block's fields may be an iterator)
     try:
         pack = _RENORM_BLOCK.pack
-        data = b"".join([pack(*r) for r in rows])
+        data = b"".join([pack(*map(int, r)) for r in rows])
         return (N.RenormBlock * max(n, 1)).from_buffer_copy(data or bytes(_RENORM_BLOCK.size))
     except struct.error:  # fields left out, or past the range of their type
-        return (N.RenormBlock * n)(*[N.RenormBlock(*r) for r in rows])
+        return (N.RenormBlock * n)(*[N.RenormBlock(*map(int, r)) for r in rows])
 
 
 def renormalize(data, u, blocks, out_len: int):
