@@ -1177,7 +1177,7 @@ __global__ __launch_bounds__(TRI_TPB) void k_eigh_tri(int nblk, const int64_t *_
     double *sy = pool + 2 * EIG_MAX_DIM;   // p, then w = p - K v; QL: sines (first buffer)
     double *sz = pool + 3 * EIG_MAX_DIM;   // QL: sines (second buffer)
     double *spart = pool + 4 * EIG_MAX_DIM;  // row-group partial sums of p
-    // (after Q is formed, the divide-and-conquer path uses the whole pool)
+    // (the divide-and-conquer path, which forms no Q, uses the whole pool once the factors are stored)
     __shared__ int srank[EIG_MAX_DIM];
     __shared__ double red[TRI_WAVES + 1];
     __shared__ double red2[TRI_WAVES + 1];  // second buffer of the reductions of the Householder steps

@@ -54,8 +54,8 @@ enum : int32_t {
 //
 // A fused two-sided segment (fused = 1) computes, for the tile's rows, the
 // intermediate slice T = P[rows, :K] Q[:K, :K2] (P = A block, Q = the input
-// block, both as above) in LDS and then C += coef * T R^T with R the
-// row-major B block read as R[c * ldr + k], k < K2.
+// block, both as above), in registers or LDS, and then C += coef * T R^T with R the
+// row-major B block read as R[c * ldr + k], k < K2 (adjoint: T R, R[k * ldr + c]).
 // A copy segment (fused = 2) adds coef * pscale[r] qscale[c] X(r, c), X the
 // input sub-matrix at element offset q with rows of ldq (a term whose block
 // factors are identities or diagonals but whose input lies elsewhere in psi:

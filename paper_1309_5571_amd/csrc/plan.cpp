@@ -256,7 +256,8 @@ struct HostPass {
 
 static uint64_t U(const void *p) { return (uint64_t)(uintptr_t)p; }
 
-// Largest intermediate width a fused two-sided segment keeps in LDS (16 rows x 64).
+// Largest intermediate width of a fused two-sided segment: a wavefront's slice of LDS
+// in the task kernel (16 rows x 64); fused.hip has it in registers, 16 columns at a time.
 constexpr int64_t FUSE_MAX_K2 = 64;
 
 // 64 x 64 tiles from this many of the longest contraction on.  One such tile sets

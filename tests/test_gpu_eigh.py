@@ -91,8 +91,9 @@ def test_eigh_random_blocks_small_and_large(seed):
 
 
 def test_eigh_kernel_boundary_orders():
-    """Orders at the edges of each kernel's range: the register reduction's row
-    counts (4, 16, 36 rows per thread up to 64, 128, 180), the global-memory
+    """Orders at the edges of each kernel's range: the register reduction (up to
+    180; 4, 8 or 12 rows per wavefront, whose edges 60 and 120 are among the
+    merges' tests), the global-memory
     reduction above 180, the last divide-and-conquer order (512: 32 panels of
     the reflector back-transformation) and the first QL one; random, rank-
     deficient, already tridiagonal (every reflector the identity) and block

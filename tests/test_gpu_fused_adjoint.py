@@ -1,4 +1,4 @@
-"""Adjoint and coefficient gradient of plans whose tiles are all 16 x 16: block
+"""Adjoint and coefficient gradient, above all of plans whose tiles are all 16 x 16: block
 orders around 1, 4, 16, 36 (one piece of a contraction) and 64 (widest intermediate
 that is fused), copy segments, tiles without a segment, more segments than the
 packed descriptors, and the outputs each asked for alone.
@@ -69,13 +69,14 @@ def test_edges(e, copies):
     _check(dm, p, dm.Plan(p, tiles=A16), e, projection.project_adjoint_sectors, projection.coef_gradient)
 
 
-def test_copies_and_gradient_in_place():
-    """Copy segments (a four-subsystem superblock), against the adjoint and the
-    gradient of its bilinear form; then gpsi written over psi itself."""
+@pytest.mark.parametrize("tile", [16, 32])
+def test_copies_and_gradient_in_place(tile):
+    """Copy segments and long segment lists (a four-subsystem superblock), against the
+    adjoint and the gradient of its bilinear form; then gpsi written over psi itself."""
     import paper_1309_5571_amd as dm
 
-    p = gen.hubbard_l11r_synthetic(96, seed=6)
-    plan = dm.Plan(p, tiles=A16)
+    p = gen.hubbard_l11r_synthetic(128, seed=6)
+    plan = dm.Plan(p, tiles=((1 << 30,), (tile,)))
 
     one = np.eye(len(p.coef))
     gradient = lambda p, psi, g: np.array([g @ l11r.project_sectors(p, psi, coef=c) for c in one])

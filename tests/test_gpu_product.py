@@ -1,6 +1,6 @@
 """The products of the density matrices and of the renormalized operators at the
-edges of their tiles (16 x 16, blocks of 16 along the contraction, four of them on
-their way) against FP64 NumPy.  Tolerance: (K + 2) u sum |a| |b| for a sum of K
+edges of their tiles (32 x 32, a 16 x 16 quarter per wavefront; panels of 32 along the
+contraction, two of them on their way) against FP64 NumPy.  Tolerance: (K + 2) u sum |a| |b| for a sum of K
 products in any order, u = 2^-53, twice for two products in turn."""
 import numpy as np
 import pytest
