@@ -244,8 +244,10 @@ static dmrg_status analyse(const dmrg_problem *p, MemberPairs *mp_out, std::vect
 
 // ------------------------------------------------------------------ pass building
 
-struct HostPass {
+struct HostPass {  // lives until the stream is synchronized (its copies' sources)
     std::vector<Task> A, B;
+    std::vector<int32_t> slot_begin;
+    std::vector<char> packed;
     std::vector<Split> splitB;          // wide passes
     int wide = 0;                       // see PassSet
     bool small = true;
@@ -823,7 +825,8 @@ struct ListUpload {
         *dst = nullptr;
         if (!v.empty()) pieces.push_back(Piece{v.data(), v.size() * sizeof(T), (void **)dst});
     }
-    dmrg_status commit(dmrg_plan *plan, hipStream_t s) {
+    // host: the packed copy's source
+    dmrg_status commit(dmrg_plan *plan, std::vector<char> &host, hipStream_t s) {
         auto padded = [](size_t n) { return (n + 255) & ~(size_t)255; };
         size_t total = 0;
         for (const Piece &p : pieces) total += padded(p.bytes);
@@ -831,7 +834,7 @@ struct ListUpload {
         char *dev = nullptr;
         DMRG_HIP(hipMalloc((void **)&dev, total));
         plan->owned.push_back(dev);
-        std::vector<char> host(total <= PACK_MAX ? total : 0);
+        host.assign(total <= PACK_MAX ? total : 0, 0);
         size_t at = 0;
         for (const Piece &p : pieces) {
             if (host.empty())
@@ -849,7 +852,8 @@ struct ListUpload {
 static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, bool low, bool pack, hipStream_t s) {
     if (pack) pack_tiles(hp, &ps.stageB.stride, &ps.stageB.dstride);
     // member-contiguous rows for the per-tile Rayleigh partials of stage B
-    std::vector<int32_t> begin(plan->nprob + 1, 0), next;
+    std::vector<int32_t> &begin = hp.slot_begin, next;
+    begin.assign(plan->nprob + 1, 0);
     for (const Task &t : hp.B) begin[t.member + 1] += 1;
     for (int m = 0; m < plan->nprob; ++m) begin[m + 1] += begin[m];
     next.assign(begin.begin(), begin.end() - 1);
@@ -861,7 +865,7 @@ static dmrg_status upload_pass(dmrg_plan *plan, HostPass &hp, PassSet &ps, bool 
     lists.add(hp.A, &ps.stageA.tasks);
     lists.add(hp.B, &ps.stageB.tasks);
     lists.add(hp.splitB, &ps.stageB.splits);
-    DMRG_TRY(lists.commit(plan, s));
+    DMRG_TRY(lists.commit(plan, hp.packed, s));
     ps.stageA.ntask = (int32_t)hp.A.size();
     ps.stageB.ntask = (int32_t)hp.B.size();
     for (const Task &t : hp.A)
@@ -1055,7 +1059,9 @@ static dmrg_status workspace_need(int32_t nprob, const dmrg_problem *probs, int3
 // coincide) and the density tiles.
 static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream, const dmrg_problem *probs) {
     // ---- forward and adjoint passes in FP64
-    HostPass f64, a64;
+    HostPass f64, a64, lo2;
+    std::vector<int32_t> ptr(1, 0), ent;
+    std::vector<ConvJob> jobs;
     build_pass(plan, false, nullptr, 0, f64);
     build_pass(plan, true, nullptr, 0, a64);
     if (f64.wide == 32) make_splits(f64, nullptr, nullptr);
@@ -1064,7 +1070,6 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
         int32_t part = 0;
         std::vector<std::vector<int32_t>> per_term(plan->nterm_total);
         gradient_slots(a64, per_term, &part);
-        std::vector<int32_t> ptr(1, 0), ent;
         for (auto &v : per_term) {
             ent.insert(ent.end(), v.begin(), v.end());
             ptr.push_back((int32_t)ent.size());
@@ -1099,9 +1104,7 @@ static dmrg_status finish_plan(dmrg_plan *plan, int32_t prec, hipStream_t stream
             plan->owned.push_back(arena);
         }
         // rebuild with the real base address (same order, so the same offsets)
-        HostPass lo2;
         build_pass(plan, false, &ls, U(arena), lo2);
-        std::vector<ConvJob> jobs;
         jobs.reserve(ls.jobs.size());
         for (const auto &j : ls.jobs)
             jobs.push_back(ConvJob{j.src, (char *)arena + j.off, j.rows, j.cols, j.diag ? 2 : (j.offdiag ? 1 : 0), 0});
