@@ -19,10 +19,10 @@
 // descriptors 1 us, operands 1.5 us, then 2 us (stage A) and 5 us (B) of
 // matrix instructions per compute unit.  Projection 37.9 us with the
 // 32-long items of the task kernel (no load ahead of its use; generic-pointer
-// loads, which can only be waited for all together), 25.1 us with k_tiles32; at
-// m = 2048 148 us -> 100 us.  For 64 members of m = 256 .. 2048 the matrix
-// instructions take 291 us of the 600: 1596 us with the task kernel, 950 us
-// with k_tiles32, 600 us (31 TFLOP/s) with k_tiles64.  Vector instructions do
+// loads, which can only be waited for all together), 25.3 us with k_tiles32; at
+// m = 2048 147 us -> 95 us.  For 64 members of m = 256 .. 2048 the matrix
+// instructions take 291 us: 1596 us with the task kernel, 950 us
+// with k_tiles32, 535 us (35 TFLOP/s) with k_tiles64.  Vector instructions do
 // not overlap the FP64 matrix instructions of their SIMD, so both keep what
 // is not a load or a product out of the item loop.
 #include "internal.h"
@@ -687,7 +687,8 @@ struct Lane64 {
 
 // MODE 0: intermediates, MODE 1: output tiles, as k_tiles32.  Three workgroups
 // per compute unit (168 registers) against two: 600 us against 658 us for the
-// 64-member projection (an item's products wait for LDS and the barrier).
+// 64-member projection, before its tiles were ordered for the XCDs (an item's
+// products wait for LDS and the barrier).
 template <int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_tiles64(
     const Task *__restrict__ tasks, const Seg *__restrict__ segs, const DiagTerm *__restrict__ diags,
