@@ -16,6 +16,8 @@
 // tile (168 registers) leave half of the tiles for a second round: 10.4 us.
 // Starting a wavefront's second segment before the first one's products: 2 %
 // slower.
+#include <type_traits>
+
 #include "internal.h"
 #include "terms.h"
 
@@ -231,10 +233,15 @@ __device__ __forceinline__ void diag_ahead(double (&v)[2], uint32_t dw, int n, c
         }
 }
 
+struct GradArgs {  // the coefficient gradient's other vector and its partials
+    const double *xg;
+    double *partials;
+};
+
 // The tile's product sums: segment w, w + FW, ... of the list on wavefront w, the
 // wavefronts' sums added in order.  stride, dstride: distance of consecutive tiles'
 // descriptors, 0 if not packed.  ADJ: a tile of the adjoint; with GRAD also the
-// coefficient gradient's share <xg, segment product> of every segment and diagonal
+// coefficient gradient's share <grad.xg, segment product> of every segment and diagonal
 // term (out, and with it coef, may be null then).  Hubbard m = 2048, calls back to
 // back, us for the adjoint / the gradient / both in one pass: 8.9 / 14.4 / 15.0 against
 // 25.2 / 29.2 / 32.1 on 32 x 32 tiles (two launches; contractions below 16 value by
@@ -243,8 +250,14 @@ template <int PREC, bool ADJ, bool GRAD>
 __global__ __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(2))) void k_fused(
     const Task *__restrict__ tasks, const Seg *__restrict__ segs, const DiagTerm *__restrict__ diags, int stride,
     int dstride, const double *__restrict__ in, const double *__restrict__ coef, const int32_t *__restrict__ mask,
-    const void *__restrict__ tmp, double *__restrict__ out, const double *__restrict__ dfold, RayArgs ray,
-    const double *__restrict__ xg, double *__restrict__ partials) {
+    const void *__restrict__ tmp, double *__restrict__ out, const double *__restrict__ dfold,
+    std::conditional_t<GRAD, GradArgs, RayArgs> extra) {
+    RayArgs ray{};
+    GradArgs grad{};
+    if constexpr (GRAD)
+        grad = extra;
+    else
+        ray = extra;
     typedef typename Ft<PREC>::acc A4;
     __shared__ double red[FW][16][17];
     __shared__ double wtile[256];  // first the diagonal terms' sums, then the output values
@@ -279,7 +292,7 @@ __global__ __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(2))) vo
         for (int v = 0; v < 4; ++v) {
             const int r = Ft<PREC>::row(g, v);
             inside[v] = r < tk.m && i < tk.n;
-            gx[v] = xg[tk.c_off + (int64_t)(tk.row0 + min(r, tk.m - 1)) * tk.ldc + tk.col0 + min(i, tk.n - 1)];
+            gx[v] = grad.xg[tk.c_off + (int64_t)(tk.row0 + min(r, tk.m - 1)) * tk.ldc + tk.col0 + min(i, tk.n - 1)];
         }
     }
     double tot[4] = {0.0, 0.0, 0.0, 0.0};
@@ -323,7 +336,7 @@ __global__ __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
         if (GRAD) {
             part = group_sum<64>(part) * s.w;
-            if (lane == 0) partials[tk.part0 + si] = part;
+            if (lane == 0) grad.partials[tk.part0 + si] = part;
         }
         s = next;
         next = segs[tk.seg_begin + min(si + 2 * FW, nseg - 1)];
@@ -334,10 +347,10 @@ __global__ __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(2))) vo
             double part = 0.0;
             for (int e = lane; e < cnt; e += 64) {
                 const int64_t rr = tk.row0 + e / tk.n, cc = tk.col0 + e % tk.n, o = rr * tk.ldc + cc;
-                part += diag_sum(diags, d, d + 1, nullptr, in[tk.x_off + o], rr, cc) * xg[tk.c_off + o];
+                part += diag_sum(diags, d, d + 1, nullptr, in[tk.x_off + o], rr, cc) * grad.xg[tk.c_off + o];
             }
             part = group_sum<64>(part);
-            if (lane == 0) partials[tk.part0 + nseg + (d - tk.diag_begin)] = part;
+            if (lane == 0) grad.partials[tk.part0 + nseg + (d - tk.diag_begin)] = part;
         }
         if (!out) return;
     }
@@ -402,20 +415,19 @@ dmrg_status launch_fused(const PassSet &ps, int prec, bool adjoint, const double
                          const RayArgs *ray, const double *xg, double *partials) {
     const Lists &l = ps.stageB;
     if (l.ntask) {
-        const RayArgs ra = ray ? *ray : RayArgs{};
-        auto go = [&](auto kernel) {
+        auto go = [&](auto kernel, auto extra) {
             hipLaunchKernelGGL(kernel, dim3(l.ntask), dim3(64 * FW), 0, s, l.tasks, (const Seg *)ps.segs,
-                               (const DiagTerm *)ps.diags, l.stride, l.dstride, in, coef, mask, tmp, out, dfold, ra, xg,
-                               partials);
+                               (const DiagTerm *)ps.diags, l.stride, l.dstride, in, coef, mask, tmp, out, dfold, extra);
         };
+        const RayArgs ra = ray ? *ray : RayArgs{};
         if (prec == DMRG_F32)
-            go(k_fused<DMRG_F32, false, false>);
+            go(k_fused<DMRG_F32, false, false>, ra);
         else if (partials)
-            go(k_fused<DMRG_F64, true, true>);
+            go(k_fused<DMRG_F64, true, true>, GradArgs{xg, partials});
         else if (adjoint)
-            go(k_fused<DMRG_F64, true, false>);
+            go(k_fused<DMRG_F64, true, false>, ra);
         else
-            go(k_fused<DMRG_F64, false, false>);
+            go(k_fused<DMRG_F64, false, false>, ra);
     }
     DMRG_HIP(hipGetLastError());
     return DMRG_OK;
