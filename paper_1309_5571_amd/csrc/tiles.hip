@@ -531,9 +531,15 @@ __global__ __launch_bounds__(64 * waves_of<MODE>()) __attribute__((amdgpu_waves_
         const int e = threadIdx.x + q * 64 * TW;
         if (e >= cnt) break;
         const int r = e / tk.n, c = e % tk.n;
-        double val = 0.0;
+        // the runs' sums in pairs: a chain of eight has half as much rounding again
+        double part[TW];
 #pragma unroll
-        for (int v = 0; v < TW; ++v) val += red[v][r][c];
+        for (int v = 0; v < TW; ++v) part[v] = red[v][r][c];
+#pragma unroll
+        for (int w = TW / 2; w > 0; w /= 2)
+#pragma unroll
+            for (int v = 0; v < w; ++v) part[v] += part[v + w];
+        double val = part[0];
         const int64_t rr = tk.row0 + r, cc = tk.col0 + c;
         const int64_t o = tk.c_off + rr * tk.ldc + cc;
         if (fold) {  // sum_d c_d vl vr, folded once for fixed coefficients
