@@ -195,7 +195,9 @@ struct OneSided {
             const double keep = scale;
             load(s, tk, in, tmp, i, g, k0);
             scale = keep;
-            piece(acc, s.K - k0, g);
+            typename Ft<PREC>::acc next = {0, 0, 0, 0};  // (a sum of its own: a shorter chain of roundings)
+            piece(next, s.K - k0, g);
+            acc += next;
         }
     }
 };
@@ -378,9 +380,8 @@ __global__ __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(2))) vo
     __syncthreads();
     if ((int)threadIdx.x < cnt) {
         const int e = rare((int)threadIdx.x), r = e / tk.n, cl = e % tk.n;
-        double val = 0.0;
-#pragma unroll
-        for (int v = 0; v < FW; ++v) val += red[v][r][cl];
+        static_assert(FW == 4, "sums in pairs");
+        double val = (red[0][r][cl] + red[1][r][cl]) + (red[2][r][cl] + red[3][r][cl]);
         if (dfold)
             val += pre_d * pre_x;
         else if (ndiag)
