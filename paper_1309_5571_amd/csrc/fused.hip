@@ -380,8 +380,9 @@ __global__ __launch_bounds__(64 * FW) __attribute__((amdgpu_waves_per_eu(2))) vo
     __syncthreads();
     if ((int)threadIdx.x < cnt) {
         const int e = rare((int)threadIdx.x), r = e / tk.n, cl = e % tk.n;
-        static_assert(FW == 4, "sums in pairs");
-        double val = (red[0][r][cl] + red[1][r][cl]) + (red[2][r][cl] + red[3][r][cl]);
+        double val = 0.0;
+#pragma unroll
+        for (int v = 0; v < FW; ++v) val += red[v][r][cl];
         if (dfold)
             val += pre_d * pre_x;
         else if (ndiag)
